@@ -15,7 +15,7 @@
 
 #include "../../include/vdwnl.h"
 #include "common.hpp"
-#include "fft_fast.hpp"
+#include "fft_split.hpp"
 
 namespace vdwnl {
 
@@ -31,6 +31,7 @@ static bool radix_plan(int n, FftPlan &p) {
     while (m % 2 == 0) { p.radix[p.nstage++] = 2; m /= 2; }
     while (m % 5 == 0) { p.radix[p.nstage++] = 5; m /= 5; }
     while (m % 3 == 0) { p.radix[p.nstage++] = 3; m /= 3; }
+    (void)split_radices(n, p.r1, p.r2);
     return m == 1 && p.nstage <= kMaxStages;
 }
 
@@ -152,7 +153,7 @@ struct Grid {
     FftPlan p1, p2, p3;
     int bmain;               // rows per theta / assemble tile
     int bnf;                 // rows per axis-3 derivative tile (and stencil tile; even)
-    int k3main;              // k3 per fused axis-1 tile (20 comps)
+    int k3main;              // columns per fused axis-1 tile (1 or 2)
     int wy20;                // axis-2 tile width of the 20 spectra
     int wdy, wdz;            // i3 per axis-2 / axis-1 derivative tile
     int shell_key;           // index into Ctx::shells
@@ -241,13 +242,14 @@ struct vdwnl_ctx {
     std::vector<InstDev> na_inst;         // instance table of the no-allocation entry point
     std::vector<double> na_E;             // its energies (host)
     struct Launch {
-        int kind, lc, off, cnt;
-        size_t lds;
-        int group;
-        int general;          // grids of the group in non-orthogonal cells
-        int mfma;             // (fused axis-1 pass) the contraction on the matrix cores
-        int var;              // radix order of the transform (its length class's variant)
-        int packed;           // (general cells) shell tables of packed upper triangles
+        int kind = 0, lc = 0, off = 0, cnt = 0;
+        size_t lds = 0;
+        int group = 0;
+        int general = 0;      // grids of the group in non-orthogonal cells
+        int mfma = 0;         // (fused axis-1 pass) the contraction on the matrix cores
+        int var = 0;          // radix order of the transform (its length class's variant)
+        int packed = 0;       // (general cells) shell tables of packed upper triangles
+        int threads = 0;      // per workgroup
     };
     // per pass: one launch per group of grids (grids whose three axes fall in
     // the same FFT length classes); the groups' chains of passes are
@@ -471,12 +473,34 @@ static int check_grid(vdwnl_ctx *c, const int32_t *shape, const double *lattice,
     return VDWNL_OK;
 }
 
+// Split class of the axis-2 passes of the 20 spectra (kLenGeneric: the
+// run-time radix passes; also where a tile's lines would exceed the LDS).
+static int y20_class(const vdwnl_ctx *c, const Grid &g) {
+    return (size_t)g.s[1] * kYC * 16 <= c->lds_cap ? split_class(g.s[1]) : kLenGeneric;
+}
+
+// LDS of a fused axis-1 tile of K columns: R1 runs of R2 slots (each run
+// padded as the kernel pads it), the slot of every frequency and the shell of
+// every item.  cs: bytes of a complex value.
+static size_t zmain_lds(const Grid &g, int K, size_t cs) {
+    const int sb = K * kNQ * (int)cs, r2 = g.p1.r2;
+    const size_t s1 = (size_t)r2 * sb + (((1 - r2) * sb) & 255);
+    return g.p1.r1 * s1 + g.s[0] * sizeof(int) + (size_t)(g.general ? g.s[0] : g.s[0] / 2 + 1) * K * sizeof(int);
+}
+
+// Threads of a fused axis-1 workgroup: an item of the wider step each (a
+// chunk of a column and one of R2 residues), at most what the kernel is
+// compiled for.
+static int zmain_threads(const Grid &g, int K, size_t cs) {
+    const int items = K * kNQ * (int)cs / 16 * g.p1.r2;
+    return std::min((items + 63) / 64 * 64, 512);
+}
+
 // Tile shapes of grid g from the LDS budget of each pass group: each tile as
 // large as the FFT tile cap and its group's budget allow (at least one unit).
 static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     const size_t cs = c->precision == 64 ? 16 : 8, rs = c->precision == 64 ? 8 : 4;
     const size_t N1 = g.s[0], N2 = g.s[1], N3 = g.s[2];
-    auto zmain = [&](size_t k3) { return (N1 + kNQ * k3 * (N1 | 1)) * cs + 16 + (N1 / 2 + 1) * k3 * sizeof(int); };
     auto xmain = [&](size_t b) { return xpass_lds(b, N3, rs); };
     auto ypass = [&](size_t w, size_t c2) { return (N2 + (N2 | 1) * w) * c2; };
     // complex elements per LDS FFT tile: bounded for the runtime-radix FFT
@@ -494,9 +518,13 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     while ((size_t)(g.bnf + 2) * N3 <= 4096 && (size_t)(g.bnf / 2 + 1) * N3 <= cap(N3) &&
            drow_lds(N3, g.bnf / 2 + 1, 16) <= kLdsCap)
         g.bnf += 2;
-    g.k3main = 1;
-    while (g.k3main < kMaxCols && (size_t)kNQ * (g.k3main + 1) * N1 <= cap(N1) && zmain(g.k3main + 1) <= c->pref[TG_Z])
-        ++g.k3main;
+    // fused axis-1 tiles: two columns (a pair k2, N2 - k2 shares its kernel
+    // rows) where they fit the budget; in FP64, whose columns are twice as
+    // large, only up to 16 KB: a second workgroup per CU is worth more than the
+    // shared rows (one column against two, us per evaluation: 96^3 FP64 469
+    // and 494, 45 x 50 x 75 168 and 176, 48^3 triclinic 177 and 186, 24^3 109
+    // and 107; in FP32 96^3 302 and 293, 160 x 160 x 320 2274 and 2160)
+    g.k3main = zmain_lds(g, 2, cs) <= std::min(c->pref[TG_Z], cs == 8 ? c->pref[TG_Z] : (size_t)16384) ? 2 : 1;
     g.wy20 = 1;
     while ((size_t)(g.wy20 + 1) * N2 <= cap(N2) && ypass(g.wy20 + 1, cs) <= c->pref[TG_Y20]) ++g.wy20;
     if (g.wy20 > 1) g.wy20 &= ~1;   // even widths: 16-byte aligned FP32 rows
@@ -790,6 +818,20 @@ static void xcd_blocks(std::vector<Tile> &t) {
     t.swap(out);
 }
 
+// The pass whose tile list a pass takes: its own, or that of the pass that
+// walks the same tiles in the other direction.
+static int tile_kind(int kind) {
+    switch (kind) {
+        case KY_20I: return KY_20F;
+        case KX_ASSEMBLE: return KX_THETA;
+        case KD_X: return KG_X;
+        case KD_Y: return KG_Y;
+        case KD_Z: return KG_Z;
+        case KF_DIV: return KF_GRAD;
+        default: return kind;
+    }
+}
+
 static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
     const bool dp = c->precision == 64;
     const size_t rs = dp ? 8 : 4, cs = 2 * rs;
@@ -818,40 +860,34 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
         for (int r = 0; r < rows; r += g.bnf) {
             const int b = std::min(g.bnf, rows - r);   // even: rows and bnf are
             tiles[fd ? KF_GRAD : KG_X].push_back({inst, r, b, 0, -1});
-            tiles[fd ? KF_DIV : KD_X].push_back({inst, r, b, 0, -1});
         }
         int slot = 0;
         for (int r = 0; r < rows; r += g.bmain) {
             const int b = std::min(g.bmain, rows - r);
             tiles[KX_THETA].push_back({inst, r, b, 0, slot++});
-            tiles[KX_ASSEMBLE].push_back({inst, r, b, 0, -1});
         }
         g.n_de = slot;
-        // axis-2 tiles of the 20 spectra
-        for (int i1 = 0; i1 < N1; ++i1)
-            for (int f = 0; f < N3h * kNQ; f += g.wy20) {
-                tiles[KY_20F].push_back({inst, i1, f, std::min(g.wy20, N3h * kNQ - f), -1});
-                tiles[KY_20I].push_back({inst, i1, f, std::min(g.wy20, N3h * kNQ - f), -1});
-            }
+        // axis-2 tiles of the 20 spectra: runs of kYC 16-byte chunks, or (no
+        // split) of wy20 complex values
+        {
+            const bool split = y20_class(c, g) != kLenGeneric;
+            const int len = split ? N3h * kNQ / (int)(16 / cs) : N3h * kNQ, w = split ? kYC : g.wy20;
+            for (int i1 = 0; i1 < N1; ++i1)
+                for (int f = 0; f < len; f += w) tiles[KY_20F].push_back({inst, i1, f, std::min(w, len - f), -1});
+        }
         // derivative tiles along axes 2 (a = i1) and 1 (a = i2): runs of i3
         if (!fd) {
             for (int i1 = 0; i1 < N1; ++i1)
-                for (int i3 = 0; i3 < N3; i3 += g.wdy) {
-                    tiles[KG_Y].push_back({inst, i1, i3, std::min(g.wdy, N3 - i3), -1});
-                    tiles[KD_Y].push_back({inst, i1, i3, std::min(g.wdy, N3 - i3), -1});
-                }
+                for (int i3 = 0; i3 < N3; i3 += g.wdy) tiles[KG_Y].push_back({inst, i1, i3, std::min(g.wdy, N3 - i3), -1});
             for (int i2 = 0; i2 < N2; ++i2)
-                for (int i3 = 0; i3 < N3; i3 += g.wdz) {
-                    tiles[KG_Z].push_back({inst, i2, i3, std::min(g.wdz, N3 - i3), -1});
-                    tiles[KD_Z].push_back({inst, i2, i3, std::min(g.wdz, N3 - i3), -1});
-                }
+                for (int i3 = 0; i3 < N3; i3 += g.wdz) tiles[KG_Z].push_back({inst, i2, i3, std::min(g.wdz, N3 - i3), -1});
         }
         // Fused axis-1 tiles: the columns k2 and N2 - k2 (the same |m2|, so
         // the same |G| shell at every (|m1|, k3)) over a run of consecutive
         // k3; one kernel row (loaded per lane) then serves four k points.  Columns
         // k2 = 0 and N2/2 stand alone.
         {
-            const int K = std::min(g.k3main, kMaxCols);
+            const int K = g.k3main;
             std::vector<Tile> zt;
             // (a budget of one column per tile: k2 and N2 - k2 in tiles of their own)
             // (general cells: every column alone, k2 over the whole axis)
@@ -881,7 +917,7 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
         g.n_ek = slot;
         // XCD-contiguous order for this grid's tiles of the other passes
         for (int k = 0; k < KIND_COUNT; ++k) {
-            if (k == KZ_MAIN) continue;
+            if (k == KZ_MAIN || tiles[k].size() == first_tile[k]) continue;
             std::vector<Tile> mine(tiles[k].begin() + first_tile[k], tiles[k].end());
             xcd_blocks(mine);
             std::copy(mine.begin(), mine.end(), tiles[k].begin() + first_tile[k]);
@@ -908,11 +944,9 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
             case KD_Z: return deriv_lds(N1, (g.wdz + 1) / 2, cs);
             case KF_GRAD: case KF_DIV: return 0;
             case KX_THETA: case KX_ASSEMBLE: return xpass_lds(g.bmain, N3, rs);
-            case KY_20F: case KY_20I: return (N2 + (N2 | 1) * g.wy20) * cs;
-            default: {   // KZ_MAIN
-                const size_t K = std::min(g.k3main, kMaxCols);
-                return (N1 + (size_t)kNQ * K * (N1 | 1)) * cs + 16 + (g.general ? N1 : N1 / 2 + 1) * K * sizeof(int);
-            }
+            case KY_20F: case KY_20I:
+                return y20_class(c, g) != kLenGeneric ? N2 * kYC * 16 : (N2 + (N2 | 1) * g.wy20) * cs;
+            default: return zmain_lds(g, g.k3main, cs);   // KZ_MAIN
         }
     };
     // the axis whose FFT a pass performs: 3 for the axis-3 passes, 2, 1
@@ -934,7 +968,7 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
             // (and the cell kind and kernel-row layout: general cells take the
             // fused pass's general variant, full or packed rows)
             const int key = ((len_class(g.s[0]) * kNumLenClasses + len_class(g.s[1])) * kNumLenClasses +
-                             len_class(g.s[2])) * 4 + (g.general ? 1 : 0) + (c->shells[g.shell_key].packed ? 2 : 0);
+                             len_class(g.s[2])) * 16 + std::min(y20_class(c, g), 3) * 4 + (g.general ? 1 : 0) + (c->shells[g.shell_key].packed ? 2 : 0);
             auto it = std::find(keys.begin(), keys.end(), key);
             group_of[gi] = (int)(it - keys.begin());
             if (it == keys.end()) keys.push_back(key);
@@ -970,25 +1004,46 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
         tiles[KZ_MAIN].swap(out);
     }
     std::vector<Tile> all;
-    for (int k = 0; k < KIND_COUNT; ++k) {
-        c->launches[k].clear();
-        for (int grp = 0; grp < c->ngroups; ++grp) {
-            vdwnl_ctx::Launch L{k, 0, (int)all.size(), 0, 0, grp, 0, 0, 0, 0};
-            for (const Tile &tl : tiles[k]) {
-                if (group_of[tl.inst] != grp) continue;
-                const Grid &g = c->grids[tl.inst];
-                L.general = g.general ? 1 : 0;
-                L.packed = c->shells[g.shell_key].packed ? 1 : 0;
-                L.mfma = (k == KZ_MAIN && c->precision == 32 && !g.general && c->contraction == VDWNL_CONTRACTION_MATRIX)
-                             ? 1 : 0;
-                // the stencil passes transform nothing (class 0 for any grid)
-                L.lc = (k == KF_GRAD || k == KF_DIV) ? 0 : len_class(axis_len(k, g));
-                L.var = (k == KF_GRAD || k == KF_DIV) ? 0 : std::min(c->variant[variant_group(k)], kNumVariants[L.lc] - 1);
-                all.push_back(tl);
-                L.lds = std::max(L.lds, lds_of(k, g));
+    {
+        std::vector<std::vector<Tile>> mine(c->ngroups);
+        std::vector<int> first(c->ngroups, 0), count(c->ngroups, 0);
+        for (int k = 0; k < KIND_COUNT; ++k) c->launches[k].clear();
+        for (int base = 0; base < KIND_COUNT; ++base) {
+            if (tile_kind(base) != base || tiles[base].empty()) continue;
+            for (const Tile &tl : tiles[base]) mine[group_of[tl.inst]].push_back(tl);
+            for (int grp = 0; grp < c->ngroups; ++grp) {
+                first[grp] = (int)all.size();
+                count[grp] = (int)mine[grp].size();
+                all.insert(all.end(), mine[grp].begin(), mine[grp].end());
+                mine[grp].clear();
             }
-            L.cnt = (int)all.size() - L.off;
-            if (L.cnt > 0) c->launches[k].push_back(L);
+            for (int k = base; k < KIND_COUNT; ++k) {
+                if (tile_kind(k) != base) continue;
+                std::vector<vdwnl_ctx::Launch> ls(c->ngroups);
+                for (size_t gi = 0; gi < c->grids.size(); ++gi) {
+                    const Grid &g = c->grids[gi];
+                    const bool plain = k == KF_GRAD || k == KF_DIV, y20 = k == KY_20F || k == KY_20I;
+                    vdwnl_ctx::Launch &L = ls[group_of[gi]];
+                    L.general = g.general ? 1 : 0;
+                    L.packed = c->shells[g.shell_key].packed ? 1 : 0;
+                    L.mfma = (k == KZ_MAIN && c->precision == 32 && !g.general &&
+                              c->contraction == VDWNL_CONTRACTION_MATRIX) ? 1 : 0;
+                    // the stencil passes transform nothing (class 0 for any grid)
+                    L.lc = plain ? 0 : y20 ? y20_class(c, g) : k == KZ_MAIN ? split_class(g.s[0]) : len_class(axis_len(k, g));
+                    L.var = (plain || y20 || k == KZ_MAIN) ? 0 : std::min(c->variant[variant_group(k)], kNumVariants[L.lc] - 1);
+                    L.threads = std::max(L.threads, k == KZ_MAIN ? zmain_threads(g, g.k3main, cs)
+                                                    : y20 && L.lc != kLenGeneric ? (kYC * g.p2.r2 + 63) / 64 * 64 : kThreads);
+                    L.lds = std::max(L.lds, lds_of(k, g));
+                }
+                for (int grp = 0; grp < c->ngroups; ++grp) {
+                    vdwnl_ctx::Launch &L = ls[grp];
+                    L.kind = k;
+                    L.off = first[grp];
+                    L.cnt = count[grp];
+                    L.group = grp;
+                    if (L.cnt > 0) c->launches[k].push_back(L);
+                }
+            }
         }
     }
     // twiddles
@@ -1049,7 +1104,7 @@ static int lds_optin(vdwnl_ctx *c) {
     hipError_t e;
     for (int k = 0; k < KIND_COUNT; ++k)
         for (const auto &L : c->launches[k]) {
-            LaunchArgs a{nullptr, nullptr, 0, L.lds, nullptr, nullptr, nullptr, nullptr, nullptr, L.general, L.mfma, L.var, L.packed};
+            LaunchArgs a{nullptr, nullptr, 0, L.lds, nullptr, nullptr, nullptr, nullptr, nullptr, L.general, L.mfma, L.var, L.packed, L.threads};
             if ((e = launch_kind(k, L.lc, c->precision, a)) != hipSuccess) return hipfail(c, e, "kernel LDS limit");
             // (and the stage probes that stand in for the pass)
             for (int pr : {PROBE_THETA_K, PROBE_U_K, PROBE_U}) {
@@ -1251,7 +1306,7 @@ static int enqueue(vdwnl_ctx *c, const DevPtrs &P, const InstDev *hinst, double 
     const int *order;
     const int npass = pass_order(c->grad_mode, &order);
     auto launch = [&](const vdwnl_ctx::Launch &L, hipStream_t s) -> int {
-        LaunchArgs a{P.inst, P.tiles + L.off, L.cnt, L.lds, P.consts, P.tw, P.twd, s, P.cols, L.general, L.mfma, L.var, L.packed};
+        LaunchArgs a{P.inst, P.tiles + L.off, L.cnt, L.lds, P.consts, P.tw, P.twd, s, P.cols, L.general, L.mfma, L.var, L.packed, L.threads};
         const hipError_t le = launch_kind(L.kind, L.lc, c->precision, a);
         return le == hipSuccess ? VDWNL_OK : hipfail(c, le, "kernel launch");
     };
@@ -1417,7 +1472,7 @@ static int probe_stage(vdwnl_ctx *c, int stage, int target, void *dst, hipStream
     }
     auto args = [&](const vdwnl_ctx::Launch &L) {
         return LaunchArgs{c->dp.inst, c->dp.tiles + L.off, L.cnt, L.lds, c->dp.consts, c->dp.tw, c->dp.twd, st, c->dp.cols,
-                          L.general, L.mfma, L.var, L.packed};
+                          L.general, L.mfma, L.var, L.packed, L.threads};
     };
     for (int i = 0; i < npass && order[i] != stop; ++i)
         for (const auto &L : c->launches[order[i]])

@@ -16,10 +16,10 @@ constexpr int kThreads = 256;                    // threads per workgroup, every
 constexpr int kTileCap = 4096;                   // complex elements of one LDS FFT tile
 constexpr int kLdsCap = 65536;                   // bytes of LDS one workgroup may take
 constexpr int kMaxStages = 16;
-constexpr int kMaxCols = 16;                     // (k2, k3) columns per fused axis-1 tile
+constexpr int kYC = 16;                          // 16-byte chunks per row of an axis-2 tile of the 20 spectra
 constexpr int kMaxMc = 64;                       // largest m_c of Eq. (Sat)
 constexpr int kMaxFd = 4;                        // largest finite-difference half-width
-constexpr int kMaxN1 = 204;                      // 20 N1 <= kTileCap (fused axis-1 pass)
+constexpr int kMaxN1 = 204;                      // (fused axis-1 pass; its lengths split into radices to 25)
 constexpr int kMaxN3 = 340;                      // 12 N3 complex doubles <= kLdsCap
 
 // One 1-D FFT length: radix sequence (each 2, 3, 4, 5 or 8) and the offset of
@@ -29,6 +29,7 @@ struct FftPlan {
     int nstage;
     int radix[kMaxStages];
     int tw;
+    int r1, r2;              // the length as two radices (fft_split.hpp), 0 where it has no such split
 };
 
 // Per-grid state seen by the kernels.  Field layouts (C order):
@@ -122,6 +123,7 @@ struct LaunchArgs {
     int mfma = 0;            // FP32 orthorhombic fused axis-1 pass: contraction on the matrix cores
     int var = 0;             // radix order of the pass's transform length (0 .. its variants - 1)
     int packed = 0;          // (general cells) the launch's shell tables hold packed upper triangles
+    int threads = kThreads;  // threads per workgroup
     void *dst = nullptr;     // (stage probes) the probe's output
     int target = 0;          // (stage probes) the grid whose tiles run
 };

@@ -21,8 +21,7 @@
 #pragma once
 
 #include "common.hpp"
-#include "fft_fast.hpp"
-#include "tile_io.hpp"
+#include "fft_split.hpp"
 
 namespace vdwnl {
 
@@ -802,14 +801,91 @@ __global__ void __launch_bounds__(kThreads) k_dcol(const InstDev *insts, const T
 
 // ---------------------------------------------------------------- axis-2 pass
 
-// The 20 spectra along axis 2.  tile: a = i1, b = first flattened (k3,
-// component) index, c = width
-template <typename T, int S, int LC, int V>
-__global__ void __launch_bounds__(kThreads) k_y(const InstDev *insts, const Tile *tiles, const void *twv) {
+// The 20 spectra along axis 2, lengths that split into two radices.  A tile is
+// kYC 16-byte chunks (256 contiguous bytes) of every row i2 of one plane:
+// step one loads its rows straight into registers (R1 16-byte loads in
+// flight per lane), step two stores its rows straight from them, and the
+// lines cross LDS once, conflict-free (16 lanes on consecutive chunks).  The
+// pass is bound by memory; crossing LDS at both ends and between the radix
+// passes, with divisions by run-time lengths outside eight lengths, had held
+// it below (with both passes changed, the evaluation of 96^3 in FP32 went
+// from 371 to 336 us, in FP64 from 565 to 518, of 90 x 100 x 108 from 653 to
+// 596, of 160 x 160 x 320 from 2337 to 2208).
+// tile: a = i1, b = first chunk of the row, c = chunks (<= kYC; the lanes
+// past them repeat the last one and store nothing).
+template <typename T, int S, int RMAX>
+__global__ void __launch_bounds__((kYC * RMAX + 63) / 64 * 64) k_y(const InstDev *insts, const Tile *tiles,
+                                                                    const void *twv) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    using K = Chunk<T>;
+    using V = typename K::V;
+    const Tile t = tiles[blockIdx.x];
+    const InstDev &I = insts[t.inst];
+    const int R1 = I.p2.r1, R2 = I.p2.r2;
+    const size_t rowc = (size_t)I.n3h * (kNQ / K::N);          // chunks per row
+    const int c = threadIdx.x % kYC, p = threadIdx.x / kYC;
+    V *g = reinterpret_cast<V *>(I.spec) + (size_t)t.a * I.n2 * rowc + t.b + min(c, t.c - 1);
+    V *lds = reinterpret_cast<V *>(smem) + c;
+    const C2<T> *tw = reinterpret_cast<const C2<T> *>(twv) + I.p2.tw;
+    if (p < R2)
+        with_radix<RMAX>(R1, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<T> w[R], x[K::N][R];
+            V in[R];
+            split_twiddles<T, S, R>(w, tw, p);
+#pragma unroll
+            for (int r = 0; r < R; ++r) in[r] = gld(g + (size_t)(p + r * R2) * rowc)[0];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                C2<T> a[K::N];
+                K::split(in[r], a);
+#pragma unroll
+                for (int q = 0; q < K::N; ++q) x[q][r] = a[q];
+            }
+#pragma unroll
+            for (int q = 0; q < K::N; ++q) Dft<T, R, S>::run(x[q]);
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                C2<T> a[K::N];
+#pragma unroll
+                for (int q = 0; q < K::N; ++q) a[q] = k == 0 ? x[q][0] : cmul(x[q][k], w[k - 1]);
+                lds[(k * R2 + p) * kYC] = K::join(a);
+            }
+        });
+    __syncthreads();
+    if (p < R1)
+        with_radix<RMAX>(R2, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<T> x[K::N][R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                C2<T> a[K::N];
+                K::split(lds[(p * R + j) * kYC], a);
+#pragma unroll
+                for (int q = 0; q < K::N; ++q) x[q][j] = a[q];
+            }
+#pragma unroll
+            for (int q = 0; q < K::N; ++q) Dft<T, R, S>::run(x[q]);
+            if (c < t.c) {
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    C2<T> a[K::N];
+#pragma unroll
+                    for (int q = 0; q < K::N; ++q) a[q] = x[q][k];
+                    gst(g + (size_t)(p + k * R1) * rowc)[0] = K::join(a);
+                }
+            }
+        });
+}
+
+// The same for any other length (the run-time radix passes).  tile: a = i1,
+// b = first flattened (k3, component) index, c = width
+template <typename T, int S>
+__global__ void __launch_bounds__(kThreads) k_y_any(const InstDev *insts, const Tile *tiles, const void *twv) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Tile t = tiles[blockIdx.x];
     const InstDev &I = insts[t.inst];
-    const int N2 = axis_len<LC>(I.n2), W = t.c, lp = N2 | 1;   // lines contiguous, odd pitch
+    const int N2 = I.n2, W = t.c, lp = N2 | 1;                 // lines contiguous, odd pitch
     C2<T> *tw = reinterpret_cast<C2<T> *>(smem);
     C2<T> *buf = tw + N2;
     const size_t rowlen = (size_t)I.n3h * kNQ;
@@ -817,161 +893,149 @@ __global__ void __launch_bounds__(kThreads) k_y(const InstDev *insts, const Tile
     rows_in_t(buf, lp, g, rowlen, N2, W);
     load_twiddles<T>(tw, I.p2, reinterpret_cast<const C2<T> *>(twv));
     __syncthreads();
-    fft_lc<T, S, LC, V>(buf, I.p2, W, 1, lp, tw);
+    fft_lc<T, S, kLenGeneric, 0>(buf, I.p2, W, 1, lp, tw);
     rows_out_t(g, rowlen, buf, lp, N2, W);
 }
 
 // ---------------------------------------------------------------- axis-1 passes
 
+// How the fused axis-1 pass forms u = phi c: on the vector ALU or the matrix
+// cores (FP32) in orthorhombic cells, where the points +-m1 of the columns k2
+// and N2 - k2 share a kernel matrix; in general cells a matrix per k point,
+// as full rows or packed upper triangles, on the vector ALU.
+enum Contraction { CT_VEC = 0, CT_MFMA = 1, CT_GEN = 2, CT_GEN_PACKED = 3 };
+
+// Sum over the workgroup in a fixed order (any number of waves up to 8);
+// result valid in thread 0.
+__device__ __forceinline__ double block_sum_n(double v) {
+    __shared__ double red[8];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < ((int)blockDim.x + 63) / 64; ++w) s += red[w];
+    return s;
+}
+
 // Forward axis-1 FFT of the 20 theta spectra, u_a(G) = sum_b phi_ab(|G|) c_b(G)
 // with c = Theta / N (Eq. Eoffk, Eq. epsofk), the energy sum
 // sum_G w_G sum_a Re(c_a^* u_a), inverse axis-1 FFT.
-// tile: a = first entry in the column list, b = number of column pairs P,
-// c = columns per pair (2: k2 and N2 - k2, which meet the same |G| shell at
-// every (|m1|, k3); 1: k2 = 0 or N2/2).  Pair i has k3 = k3_0 + i; the list
-// holds the columns pair by pair.
+// tile: a = first entry in the column list, b = items per |m1| (P: 1 or 2
+// consecutive k3), c = columns per item (CP: 2 = k2 and N2 - k2, which meet the
+// same |G| shell at every (|m1|, k3), then P = 1; else 1).  The list holds
+// the tile's P CP <= 2 columns.
 //
-// Contraction layout: lanes form groups of kNQ (three per wave).  A group
-// takes one item, a |m1| and a pair; lane a loads row a of that shell's
-// kernel matrix (kNQ contiguous values, 16-byte loads) into registers and
-// forms u_a at the pair's points (+-m1 of each column).  The rows of the
-// group's next item are loaded meanwhile (two register sets in turn).
-// GEN (grids in non-orthogonal cells): every item is one k point with its
-// own shell; lane a loads row a of its full matrix, or (PK: the launch's
-// tables hold packed upper triangles) gathers the row from it through
-// offsets fixed per lane.
-// PROBE (parity probes of the stages, never in an evaluation): 1 writes the
+// The transforms are split ones (fft_split.hpp): the tile's rows (plane i1,
+// 160 bytes per column in FP32) go between global memory and registers in
+// 16-byte chunks, and LDS holds slot k1 R2 + j (later k1 R2 + k2, the
+// frequency k1 + R1 k2) with the tile's components contiguous, so every step
+// moves whole chunks, 16 bytes a lane, and works in place: four barriers in
+// all.  A padding after each R2 slots keeps the lanes of neighbouring items on
+// different banks.  The contraction reads the 20 components of a point as
+// contiguous chunks too.  (The radix passes it replaces crossed LDS in words
+// of 8 bytes, at both ends and in every pass: the fused pass alone went from
+// 90 to 52 us at 96^3 in FP32, from 160 to 69 at 90 x 100 x 108, from 154 to
+// 140 at 128^3, and from 20 to 10 at 24^3 in FP64.)
+//
+// Contraction layout (vector ALU): lanes form groups of kNQ (three per wave).
+// A group takes one item, a |m1| and a column or pair; lane a loads row a of
+// that shell's kernel matrix (kNQ contiguous values, 16-byte loads) into
+// registers and forms u_a at the item's points (+-m1 of each column).  The
+// rows of the group's next item are loaded meanwhile (two register sets in
+// turn).  CT_GEN: every item is one k point with its own shell; lane a loads
+// row a of its full matrix, or (packed) gathers the row through offsets fixed
+// per lane.
+// probe (parity probes of the stages, never in an evaluation): 1 writes the
 // forward spectra c = FFT(theta)/N back in place of the tile (no contraction,
 // no inverse); 2 writes u = phi c (no inverse); 0 is the evaluation.
-// MF (FP32, orthorhombic cells): the contraction on the matrix cores (see the
-// item loop below) instead of the vector ALU; the same items, the same
-// results up to the order of the FP32 additions.
-template <typename T, int LC, int V, bool GEN, int PROBE, bool MF, bool PK>
-__global__ void __launch_bounds__(kThreads) k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols,
-                                                     const void *twv) {
+template <typename T, int CT, int RMAX>
+__global__ void __launch_bounds__(sizeof(T) == 4 ? (20 * RMAX + 63) / 64 * 64 : 512)
+k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *twv, int probe) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int kGroups = (kThreads / 64) * (64 / kNQ);   // lane groups per workgroup
-    constexpr int kEpc = 16 / (int)sizeof(C2<T>);             // complex values per 16-byte chunk
+    using Ch = Chunk<T>;
+    using V = typename Ch::V;
+    constexpr bool GEN = CT == CT_GEN || CT == CT_GEN_PACKED, PK = CT == CT_GEN_PACKED, MF = CT == CT_MFMA;
+    static_assert(!MF || sizeof(T) == 4, "matrix-core contraction: FP32");
+    constexpr int kCpc = kNQ / Ch::N;                          // chunks per column
+    constexpr int kColB = kNQ * (int)sizeof(C2<T>);            // bytes per column of a slot
     const Tile t = tiles[blockIdx.x];
     const InstDev &I = insts[t.inst];
-    const int N1 = axis_len<LC>(I.n1), N2 = I.n2, N3 = I.n3, N3h = I.n3h, P = t.b, CP = t.c, K = P * CP;
-    const int W = K * kNQ, lp = N1 | 1;                      // W lines, contiguous, odd pitch
-    const int cstride = kNQ * lp;                             // LDS elements per column
-    __shared__ int colbase[kMaxCols];                         // offset of each column in a k1 plane
-    C2<T> *twall = reinterpret_cast<C2<T> *>(smem);
-    C2<T> *buf = twall + N1;
-    int *sidx = reinterpret_cast<int *>(buf + W * lp);        // shell of every item
-    {
-        const int2 cw = cols[t.a + min((int)threadIdx.x, K - 1)];   // unconditional (clamped) load
-        if ((int)threadIdx.x < K) colbase[threadIdx.x] = (cw.x * N3h + cw.y) * kNQ;
-    }
-    const int2 c0 = cols[t.a];
-    __syncthreads();
-    const size_t plane = (size_t)N2 * N3h * kNQ;
+    const int N1 = I.n1, N2 = I.n2, N3 = I.n3, N3h = I.n3h, P = t.b, CP = t.c, K = P * CP;
+    const int R1 = I.p1.r1, R2 = I.p1.r2;
+    const int nt = blockDim.x, C = K * kCpc;                   // chunks per slot
+    const int sb = K * kColB;                                  // bytes per slot
+    const int s1 = R2 * sb + (((1 - R2) * sb) & 255);          // bytes per R2 slots: lanes C apart go on where C stop
+    unsigned char *buf = smem;
+    int *soff = reinterpret_cast<int *>(smem + R1 * s1);       // slot offset of frequency k
+    int *sidx = soff + N1;                                     // shell of every item
+    const int2 c0 = cols[t.a], c1 = cols[t.a + K - 1];
+    const C2<T> *tw = reinterpret_cast<const C2<T> *>(twv) + I.p1.tw;
+    const size_t plane = (size_t)N2 * N3h * kNQ;               // complex values
     C2<T> *spec = reinterpret_cast<C2<T> *>(I.spec);
-    // 16-byte chunks (l, w, e): plane l, column w, chunk e of the column's 20
-    // values.  Each thread keeps one chunk column (w, e) and steps through the
-    // planes; the loads of U planes are issued before their LDS writes (U at
-    // least the planes per lane where that is at most 12: one batch).
-    constexpr int kCpc = kNQ / kEpc;                          // chunks per column
-    auto io_batch = [&](bool in, int C, int rps, auto Uc) {
-        constexpr int U = decltype(Uc)::value;
-        const int r0 = threadIdx.x / C, c = threadIdx.x - r0 * C, w = c / kCpc, e = c - w * kCpc;
-        C2<T> *lb = buf + (w * kNQ + e * kEpc) * lp;
-        // this lane's chunk column; planes l = r0 + s rps, s = j U + u
-        char *cb = reinterpret_cast<char *>(spec + colbase[w] + e * kEpc);
-        const size_t plane_bytes = plane * sizeof(C2<T>);
-        for (int l0 = r0; l0 < N1; l0 += U * rps) {
-            T ra[U], rb[U], rc[U], rd[U];
-            if (in) {
-                // unconditional loads (a plane past N1 re-reads plane r0, valid here)
+    C2<T> *col0 = spec + (size_t)(c0.x * N3h + c0.y) * kNQ, *col1 = spec + (size_t)(c1.x * N3h + c1.y) * kNQ;
+    // orthorhombic cell: item = |m1| P + pr, the +-m1 points share a shell;
+    // general cell: item = k1 P + pr over the whole axis, a shell each
+    const int k30 = c0.y, m2 = GEN ? c0.x : freq_abs(c0.x, N2);
+    const int nitems = (GEN ? N1 : N1 / 2 + 1) * P;
+    const gptr<const int> smap = gld(I.shellmap + (size_t)m2 * N3h + k30);
+    const size_t smap_m1 = (size_t)(GEN ? N2 : I.h2) * N3h;
+    // the thread's first shell index is loaded before the tile (clamped,
+    // unconditional) and stored after it
+    auto smap_at = [&](int i) { return smap[(size_t)(i >> (P - 1)) * smap_m1 + (i & (P - 1))]; };
+    const int sh_first = smap_at(min((int)threadIdx.x, nitems - 1));
+
+    // step one of the forward transform: rows -> registers -> slots
+    for (int it = threadIdx.x; it < C * R2; it += nt) {
+        const int p = it / C, c = it - p * C, w = c / kCpc, e = c - w * kCpc;
+        const V *g = reinterpret_cast<const V *>((w ? col1 : col0) + (size_t)p * plane) + e;
+        unsigned char *lb = buf + p * sb + c * 16;
+        const size_t step = (size_t)R2 * plane * sizeof(C2<T>);
+        with_radix<RMAX>(R1, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<T> tf[R], x[Ch::N][R];
+            V in[R];
+            split_twiddles<T, -1, R>(tf, tw, p);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int l = l0 + u * rps;
-                    const char *src = cb + (size_t)(uint32_t)(l < N1 ? l : r0) * plane_bytes;
-                    if constexpr (kEpc == 2) {
-                        const float4 v = gld(reinterpret_cast<const float4 *>(src))[0];
-                        ra[u] = v.x; rb[u] = v.y; rc[u] = v.z; rd[u] = v.w;
-                    } else {
-                        const C2<T> v = gld(reinterpret_cast<const C2<T> *>(src))[0];
-                        ra[u] = v.x; rb[u] = v.y;
-                    }
-                }
+            for (int r = 0; r < R; ++r) in[r] = gld(reinterpret_cast<const V *>(reinterpret_cast<const char *>(g) + r * step))[0];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                C2<T> a[Ch::N];
+                Ch::split(in[r], a);
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) x[q][r] = a[q];
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int l = l0 + u * rps;
-                if (l >= N1) continue;
-                char *dst = cb + (size_t)(uint32_t)l * plane_bytes;
-                if (in) {
-                    lb[l] = mk<T>(ra[u], rb[u]);
-                    if constexpr (kEpc == 2) lb[lp + l] = mk<T>(rc[u], rd[u]);
-                } else if constexpr (kEpc == 2) {
-                    const C2<T> p0 = lb[l], p1 = lb[lp + l];
-                    gst(reinterpret_cast<float4 *>(dst))[0] = make_float4(p0.x, p0.y, p1.x, p1.y);
-                } else {
-                    gst(reinterpret_cast<C2<T> *>(dst))[0] = lb[l];
-                }
-            }
-        }
-    };
-    auto io = [&](bool in) {
-        const int C = K * kCpc;                               // chunks per plane
-        if (C > kThreads) {                                   // (only tiny N1 with many columns)
-            const int total = N1 * C;
-            for (int i = threadIdx.x; i < total; i += kThreads) {
-                const int l = i / C, c = i - l * C, w = c / kCpc, e = c - w * kCpc;
-                C2<T> *lb = buf + (w * kNQ + e * kEpc) * lp + l;
-                C2<T> *gb = spec + (size_t)l * plane + colbase[w] + e * kEpc;
+            for (int q = 0; q < Ch::N; ++q) Dft<T, R, -1>::run(x[q]);
 #pragma unroll
-                for (int q = 0; q < kEpc; ++q) {
-                    if (in) lb[q * lp] = gld(gb)[q];
-                    else gst(gb)[q] = lb[q * lp];
-                }
+            for (int k = 0; k < R; ++k) {
+                C2<T> a[Ch::N];
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) a[q] = k == 0 ? x[q][0] : cmul(x[q][k], tf[k - 1]);
+                *reinterpret_cast<V *>(lb + k * s1) = Ch::join(a);
             }
-            return;
-        }
-        const int rps = kThreads / C;                         // planes per step
-        if ((int)threadIdx.x >= rps * C) return;
-        const int steps = (N1 + rps - 1) / rps;               // planes per lane
-        if (steps > kUnroll && steps <= 12) io_batch(in, C, rps, std::integral_constant<int, 12>{});
-        else io_batch(in, C, rps, std::integral_constant<int, kUnroll>{});
-    };
-    const T *tab = reinterpret_cast<const T *>(I.shelltab);
-    // orthorhombic cell: item = |m1| P + pair, the +-m1 points share a shell;
-    // general cell: item = k1 P + pair over the whole axis, a shell each
-    constexpr bool general = GEN;
-    const int k30 = c0.y;
-    const int m2 = general ? c0.x : freq_abs(c0.x, N2);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        });
+    }
+    for (int k = threadIdx.x; k < N1; k += nt) {
+        const int q = k / R1;
+        soff[k] = (k - q * R1) * s1 + q * sb;
+    }
+    if ((int)threadIdx.x < nitems) sidx[threadIdx.x] = sh_first;
+    for (int i = threadIdx.x + nt; i < nitems; i += nt) sidx[i] = smap_at(i);
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ngroups = (nt >> 6) * (64 / kNQ);
     const int grp = lane / kNQ, al = lane - grp * kNQ;
     const bool lane_on = grp < 64 / kNQ;
     const int gid = wave * (64 / kNQ) + grp;
-    const int nitems = (general ? N1 : N1 / 2 + 1) * P;
-    // shell of every item, into LDS; the thread's first item is loaded
-    // before the tile (unconditionally, index clamped), so that its latency
-    // overlaps the tile's loads
-    const gptr<const int> smap = gld(I.shellmap + (size_t)m2 * N3h + k30);
-    const size_t smap_m1 = (size_t)(general ? N2 : I.h2) * N3h;
-    auto smap_at = [&](int i) {
-        const int m1 = i / P;
-        return smap[m1 * smap_m1 + (i - m1 * P)];
-    };
-    const int sh_first = smap_at(min((int)threadIdx.x, nitems - 1));
-    io(true);
-    load_twiddles<T>(twall, I.p1, reinterpret_cast<const C2<T> *>(twv));
-    if ((int)threadIdx.x < nitems) sidx[threadIdx.x] = sh_first;
-    for (int i = threadIdx.x + kThreads; i < nitems; i += kThreads) sidx[i] = smap_at(i);
     // (packed rows: entry (r, q), r <= q, at r kNQ - r (r - 1)/2 + q - r)
-    int poff[GEN && PK ? kNQ : 1];
-    if constexpr (GEN && PK) {
+    int poff[PK ? kNQ : 1];
+    if constexpr (PK) {
 #pragma unroll
         for (int b = 0; b < kNQ; ++b) {
             const int r = min(al, b), q = max(al, b);
             poff[b] = r * kNQ - ((r * (r - 1)) >> 1) + q - r;
         }
     }
-    static_assert(!MF || (sizeof(T) == 4 && !GEN), "matrix-core contraction: FP32, orthorhombic cells");
     // the kernel-matrix row this lane holds: a of its group (vector ALU), or
     // 4 rb + (lane % 4) of its block (matrix cores, below)
     const int mf_blk = lane >> 2, mf_q = lane & 3;
@@ -979,100 +1043,78 @@ __global__ void __launch_bounds__(kThreads) k_z_main(const InstDev *insts, const
     const int mf_g = mf_on ? mf_blk / 5 : 2;
     const int mf_rb = mf_on ? mf_blk - (mf_blk / 5) * 5 : 0;
     const int row = MF ? 4 * mf_rb + mf_q : al;
+    const T *tab = reinterpret_cast<const T *>(I.shelltab);
     // row `row` of the shell matrix of an item (index clamped to the last
     // item: the loads stay unconditional)
     auto fetch = [&](int item, T *f) {
         const int sh = sidx[min(item, nitems - 1)];
-        if constexpr (GEN && PK) {
+        if constexpr (PK) {
             const gptr<const T> src = gld(tab + (size_t)sh * kTabPacked);
 #pragma unroll
             for (int b = 0; b < kNQ; ++b) f[b] = src[poff[b]];
-            return;
-        }
-        const gptr<const T> src = gld(tab + (size_t)sh * kTabRow + row * kNQ);
-        if constexpr (sizeof(T) == 4) {
-            const gptr<const float4> s4 = (gptr<const float4>)src;
-#pragma unroll
-            for (int q = 0; q < kNQ / 4; ++q) {
-                const float4 v = s4[q];
-                f[4 * q] = v.x; f[4 * q + 1] = v.y; f[4 * q + 2] = v.z; f[4 * q + 3] = v.w;
-            }
         } else {
-            const gptr<const double2> s2 = (gptr<const double2>)src;
+            const gptr<const V> src = gld(reinterpret_cast<const V *>(tab + (size_t)sh * kTabRow + row * kNQ));
+            constexpr int E = 16 / (int)sizeof(T);
 #pragma unroll
-            for (int q = 0; q < kNQ / 2; ++q) {
-                const double2 v = s2[q];
-                f[2 * q] = v.x; f[2 * q + 1] = v.y;
+            for (int q = 0; q < kNQ / E; ++q) {
+                const V v = src[q];
+                if constexpr (sizeof(T) == 4) { f[4 * q] = v.x; f[4 * q + 1] = v.y; f[4 * q + 2] = v.z; f[4 * q + 3] = v.w; }
+                else { f[2 * q] = v.x; f[2 * q + 1] = v.y; }
             }
         }
     };
     __syncthreads();
     // kernel rows in flight: one item (vector ALU) or round (matrix cores)
-    // ahead, the first before the forward FFT
+    // ahead, the first before step two
     T fa[kNQ], fb[kNQ];
     const int it0 = MF ? wave * (64 / kNQ) + mf_g : gid;
-    if (PROBE != 1 && (MF || lane_on)) fetch(it0, fa);
-    fft_lc<T, -1, LC, V>(buf, I.p1, W, 1, lp, twall);
-    if constexpr (PROBE == 1) {
-        const T inv_n = (T)I.inv_n;
-        for (int i = threadIdx.x; i < W * lp; i += kThreads) buf[i] = cscale(buf[i], inv_n);
-        __syncthreads();
-        io(false);
+    if (MF || lane_on) fetch(it0, fa);
+    // step two: the slots of (chunk, k1), in place
+    for (int it = threadIdx.x; it < C * R1; it += nt) {
+        const int p = it / C, c = it - p * C;
+        unsigned char *lb = buf + p * s1 + c * 16;
+        with_radix<RMAX>(R2, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<T> x[Ch::N][R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                C2<T> a[Ch::N];
+                Ch::split(*reinterpret_cast<const V *>(lb + j * sb), a);
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) x[q][j] = a[q];
+            }
+#pragma unroll
+            for (int q = 0; q < Ch::N; ++q) Dft<T, R, -1>::run(x[q]);
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                C2<T> a[Ch::N];
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) a[q] = x[q][k];
+                *reinterpret_cast<V *>(lb + k * sb) = Ch::join(a);
+            }
+        });
+    }
+    __syncthreads();
+
+    // (probes) the tile's spectrum to its rows
+    auto store_spectrum = [&](T scale) {
+        for (int it = threadIdx.x; it < C * N1; it += nt) {
+            const int k = it / C, c = it - k * C, w = c / kCpc, e = c - w * kCpc;
+            C2<T> a[Ch::N];
+            Ch::split(*reinterpret_cast<const V *>(buf + soff[k] + c * 16), a);
+            for (int q = 0; q < Ch::N; ++q) a[q] = cscale(a[q], scale);
+            gst(reinterpret_cast<V *>((w ? col1 : col0) + (size_t)k * plane) + e)[0] = Ch::join(a);
+        }
+    };
+    const T inv_n = (T)I.inv_n;
+    if (probe == 1) {
+        store_spectrum(inv_n);
         if (threadIdx.x == 0) I.part_ek[t.slot] = 0.0;
         return;
     }
-
-    const T inv_n = (T)I.inv_n;
     const double wn = (double)inv_n * (double)inv_n;
     double e = 0.0;
-    // item it = m1 P + pr, stepped by kGroups without divisions
-    const int dm = kGroups / P, dr = kGroups - dm * P;
-    int m1 = gid / P, pr = gid - m1 * P;
-    // u at the points of the current item with the kernel row f; a group's
-    // lanes share one wave, so reads of theta and writes of u need wave-level
-    // ordering only
-    auto process = [&](const T *f) {
-        // the points +-m1 of each column of the item (lq = l for k1 = 0, the
-        // Nyquist plane and general cells: the second point is the first
-        // again, its energy masked and its u the same value written twice)
-        const int l = m1;
-        int lq = N1 - m1;
-        const bool two = !(general || m1 == 0 || lq == m1);
-        if (!two) lq = l;
-        const T mask2 = two ? (T)1 : (T)0;
-        const int w0 = __mul24(pr, CP);
-        const int k3 = k30 + pr;                               // the item's columns share k3
-        const bool edge = (k3 == 0) || ((N3 & 1) == 0 && 2 * k3 == N3);
-        const double wgt = edge ? wn : 2.0 * wn;
-        m1 += dm;
-        pr += dr;
-        if (pr >= P) { pr -= P; ++m1; }
-        auto column = [&](int w) {
-            C2<T> u1 = mk<T>((T)0, (T)0), u2 = u1;
-            C2<T> *xc = buf + __mul24(w, cstride);
-            C2<T> *x1 = xc + l;                                   // component b at x1[b lp]
-            C2<T> *x2 = xc + lq;
-#pragma unroll
-            for (int b = 0; b < kNQ; ++b) {
-                const C2<T> t1 = x1[b * lp], t2 = x2[b * lp];
-                u1.x += f[b] * t1.x;
-                u1.y += f[b] * t1.y;
-                u2.x += f[b] * t2.x;
-                u2.y += f[b] * t2.y;
-            }
-            const C2<T> own1 = x1[al * lp], own2 = x2[al * lp];
-            e += wgt * (double)(own1.x * u1.x + own1.y * u1.y + mask2 * (own2.x * u2.x + own2.y * u2.y));
-            // every lane of the group has read theta at these points before
-            // any lane overwrites its component with u; the next column or
-            // item reads other points (each k point belongs to one item), so
-            // no ordering is needed after the writes
-            wave_sync();
-            x1[al * lp] = cscale(u1, inv_n);
-            x2[al * lp] = cscale(u2, inv_n);
-        };
-        column(w0);
-        if (CP == 2) column(w0 + 1);
-    };
+    auto weight = [&](int k3) { return (k3 == 0 || ((N3 & 1) == 0 && 2 * k3 == N3)) ? wn : 2.0 * wn; };
     if constexpr (MF) {
         // Matrix cores: v_mfma_f32_4x4x1_16b_f32 forms 16 independent 4 x 4
         // outer products per instruction (A 4 x 1 and B 1 x 4 per block,
@@ -1081,99 +1123,181 @@ __global__ void __launch_bounds__(kThreads) k_z_main(const InstDev *insts, const
         // in use): item g = k / 5 of the three, rows 4 rb .. 4 rb + 3 of its
         // kernel matrix (rb = k % 5).  Lane 4 k + i feeds A = row 4 rb + i of
         // the matrix (20 values in registers, one per K step b) and B =
-        // column i of the item's four real columns: theta_b at point i / 2
-        // (+m1 or -m1) and part i % 2 (re, im); it receives in its four
-        // accumulators u_{4 rb + r} at that point and part, r = 0..3.  Items
-        // of a column pair (two columns sharing every shell) instead use
-        // B column i = theta_b at column i % 2 and point i / 2, both parts
-        // from one 8-byte LDS read, in two chains (real and imaginary parts:
-        // the kernel is real); the accumulators hold u_{4 rb + r} at that
-        // column and point.  The lanes of a wave read theta before any of
-        // them writes u (wave-level ordering), as on the vector path.
+        // theta_b at column i % 2 of the item's pair and point i / 2 (+m1 or
+        // -m1), real and imaginary parts in two chains (the kernel is real);
+        // it receives in its four accumulators u_{4 rb + r}, r = 0..3, at that
+        // column and point.  An item of one column (k2 = 0 and N2/2) gives
+        // both lanes of a point the same column (the same values written
+        // twice).  The lanes of a wave read theta before any of them writes u
+        // (wave-level ordering), as on the vector path.
         typedef float v4f __attribute__((ext_vector_type(4)));
         const int g0 = wave * (64 / kNQ);
         int it = g0 + mf_g;
-        int mg = it / P, pg = it - mg * P;
         const float fin = (float)I.inv_n;
         auto process_mf = [&](const T *f) {
             const bool valid = mf_on && it < nitems;
-            const int l = valid ? mg : 0;                 // (an item past the end reads point 0)
+            const int l = valid ? it >> (P - 1) : 0, pg = it & (P - 1);   // (an item past the end reads point 0)
             int lq = N1 - l;
             const bool two = !(l == 0 || lq == l);
             if (!two) lq = l;
-            const int w0 = __mul24(pg, CP);
-            const int k3 = k30 + pg;
-            const bool edge = (k3 == 0) || ((N3 & 1) == 0 && 2 * k3 == N3);
-            const double wgt = (valid && (mf_q < 2 || two)) ? (edge ? wn : 2.0 * wn) : 0.0;
-            it += kGroups;
-            mg += dm;
-            pg += dr;
-            if (pg >= P) { pg -= P; ++mg; }
-            if (CP == 2) {
-                // lane column: column mf_q % 2 of the pair, point +m1 (mf_q < 2) or -m1
-                C2<T> *xc = buf + __mul24(w0 + (mf_q & 1), cstride) + (mf_q < 2 ? l : lq);
-                C2<T> *oc = xc + 4 * mf_rb * lp;
-                // every LDS read of the round before the first product (one
-                // wait instead of one per K step)
-                C2<T> th[kNQ], own[4];
+            const double wgt = (valid && (mf_q < 2 || two) && (CP == 2 || !(mf_q & 1))) ? weight(k30 + pg) : 0.0;
+            it += ngroups;
+            unsigned char *xc = buf + soff[mf_q < 2 ? l : lq] + (CP == 2 ? mf_q & 1 : pg) * kColB;
+            float4 *oc = reinterpret_cast<float4 *>(xc + 4 * mf_rb * (int)sizeof(C2<T>));
+            // every LDS read of the round before the first product (one
+            // wait instead of one per K step)
+            float4 th[kNQ / 2];
 #pragma unroll
-                for (int b = 0; b < kNQ; ++b) th[b] = xc[b * lp];
+            for (int b = 0; b < kNQ / 2; ++b) th[b] = reinterpret_cast<const float4 *>(xc)[b];
+            const float4 o0 = oc[0], o1 = oc[1];
+            __builtin_amdgcn_sched_barrier(0);
+            v4f are = {0.f, 0.f, 0.f, 0.f}, aim = are;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) own[r] = oc[r * lp];
-                __builtin_amdgcn_sched_barrier(0);
-                v4f are = {0.f, 0.f, 0.f, 0.f}, aim = are;
-#pragma unroll
-                for (int b = 0; b < kNQ; ++b) {
-                    are = __builtin_amdgcn_mfma_f32_4x4x1f32(f[b], th[b].x, are, 0, 0, 0);
-                    aim = __builtin_amdgcn_mfma_f32_4x4x1f32(f[b], th[b].y, aim, 0, 0, 0);
-                }
-                float es = 0.f;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) es += own[r].x * are[r] + own[r].y * aim[r];
-                e += wgt * (double)es;
-                wave_sync();
-                if (valid) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) oc[r * lp] = mk<T>(are[r] * fin, aim[r] * fin);
-                }
-            } else {
-                const int pt = mf_q < 2 ? l : lq;
-                float *x0 = reinterpret_cast<float *>(buf + __mul24(w0, cstride) + pt) + (mf_q & 1);
-                float *o0 = x0 + 2 * 4 * mf_rb * lp;
-                v4f a0 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int b = 0; b < kNQ; ++b) a0 = __builtin_amdgcn_mfma_f32_4x4x1f32(f[b], x0[2 * b * lp], a0, 0, 0, 0);
-                e += wgt * (double)(o0[0] * a0[0] + o0[2 * lp] * a0[1] + o0[4 * lp] * a0[2] + o0[6 * lp] * a0[3]);
-                wave_sync();
-                if (valid) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) o0[2 * r * lp] = a0[r] * fin;
-                }
+            for (int b = 0; b < kNQ / 2; ++b) {
+                are = __builtin_amdgcn_mfma_f32_4x4x1f32(f[2 * b], th[b].x, are, 0, 0, 0);
+                aim = __builtin_amdgcn_mfma_f32_4x4x1f32(f[2 * b], th[b].y, aim, 0, 0, 0);
+                are = __builtin_amdgcn_mfma_f32_4x4x1f32(f[2 * b + 1], th[b].z, are, 0, 0, 0);
+                aim = __builtin_amdgcn_mfma_f32_4x4x1f32(f[2 * b + 1], th[b].w, aim, 0, 0, 0);
+            }
+            const float es = o0.x * are[0] + o0.y * aim[0] + o0.z * are[1] + o0.w * aim[1] +
+                             o1.x * are[2] + o1.y * aim[2] + o1.z * are[3] + o1.w * aim[3];
+            e += wgt * (double)es;
+            wave_sync();
+            if (valid) {
+                oc[0] = make_float4(are[0] * fin, aim[0] * fin, are[1] * fin, aim[1] * fin);
+                oc[1] = make_float4(are[2] * fin, aim[2] * fin, are[3] * fin, aim[3] * fin);
             }
         };
         // rounds of three items per wave, the loop bound uniform over the wave
-        for (int base = g0; base < nitems; base += 2 * kGroups) {
-            fetch(it + kGroups, fb);               // the next round's row (clamped past the end)
+        for (int base = g0; base < nitems; base += 2 * ngroups) {
+            fetch(it + ngroups, fb);               // the next round's row (clamped past the end)
             process_mf(fa);
-            if (base + kGroups >= nitems) break;
-            fetch(it + kGroups, fa);
+            if (base + ngroups >= nitems) break;
+            fetch(it + ngroups, fa);
             process_mf(fb);
         }
     } else {
+        // u at the points of item `it` with the kernel row f; a group's lanes
+        // share one wave, so reads of theta and writes of u need wave-level
+        // ordering only
+        auto process = [&](int it, const T *f) {
+            // the points +-m1 of each column of the item (lq = l for k1 = 0 and
+            // the Nyquist plane: the second point is the first again, its
+            // energy masked and its u the same value written twice); one
+            // point in general cells
+            const int l = it >> (P - 1), pr = it & (P - 1);
+            int lq = N1 - l;
+            const bool two = !(GEN || l == 0 || lq == l);
+            if (!two) lq = l;
+            const T mask2 = two ? (T)1 : (T)0;
+            const double wgt = weight(k30 + pr);
+            const int o1 = soff[l], o2 = soff[lq];
+            auto column = [&](int w) {
+                C2<T> u1 = mk<T>((T)0, (T)0), u2 = u1;
+                C2<T> *x1 = reinterpret_cast<C2<T> *>(buf + o1 + w * kColB), *x2 = reinterpret_cast<C2<T> *>(buf + o2 + w * kColB);
+#pragma unroll
+                for (int b = 0; b < kCpc; ++b) {
+                    C2<T> t1[Ch::N], t2[Ch::N];
+                    Ch::split(reinterpret_cast<const V *>(x1)[b], t1);
+                    if (!GEN) Ch::split(reinterpret_cast<const V *>(x2)[b], t2);
+#pragma unroll
+                    for (int q = 0; q < Ch::N; ++q) {
+                        u1.x += f[Ch::N * b + q] * t1[q].x;
+                        u1.y += f[Ch::N * b + q] * t1[q].y;
+                        if (!GEN) {
+                            u2.x += f[Ch::N * b + q] * t2[q].x;
+                            u2.y += f[Ch::N * b + q] * t2[q].y;
+                        }
+                    }
+                }
+                const C2<T> own1 = x1[al];
+                T es = own1.x * u1.x + own1.y * u1.y;
+                if (!GEN) {
+                    const C2<T> own2 = x2[al];
+                    es += mask2 * (own2.x * u2.x + own2.y * u2.y);
+                }
+                e += wgt * (double)es;
+                // every lane of the group has read theta at these points before
+                // any lane overwrites its component with u; the next column or
+                // item reads other points (each k point belongs to one item),
+                // so no ordering is needed after the writes
+                wave_sync();
+                x1[al] = cscale(u1, inv_n);
+                if (!GEN) x2[al] = cscale(u2, inv_n);
+            };
+            column(CP == 2 ? 0 : pr);
+            if (CP == 2) column(1);
+        };
         for (int it = gid; lane_on && it < nitems;) {
-            fetch(it + kGroups, fb);               // the next item's row (clamped past the end)
-            process(fa);
-            it += kGroups;
+            fetch(it + ngroups, fb);               // the next item's row (clamped past the end)
+            process(it, fa);
+            it += ngroups;
             if (it >= nitems) break;
-            fetch(it + kGroups, fa);
-            process(fb);
-            it += kGroups;
+            fetch(it + ngroups, fa);
+            process(it, fb);
+            it += ngroups;
         }
     }
     __syncthreads();
-    if constexpr (PROBE == 0) fft_lc<T, 1, LC, V>(buf, I.p1, W, 1, lp, twall);
-    io(false);
-    const double sum = block_sum(e);
+    if (probe == 2) {
+        store_spectrum((T)1);
+        return;
+    }
+    // the inverse transform: step two backwards, in place
+    for (int it = threadIdx.x; it < C * R1; it += nt) {
+        const int p = it / C, c = it - p * C;
+        unsigned char *lb = buf + p * s1 + c * 16;
+        with_radix<RMAX>(R2, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<T> tf[R], x[Ch::N][R];
+            split_twiddles<T, 1, R>(tf, tw, p);
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                C2<T> a[Ch::N];
+                Ch::split(*reinterpret_cast<const V *>(lb + k * sb), a);
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) x[q][k] = a[q];
+            }
+#pragma unroll
+            for (int q = 0; q < Ch::N; ++q) Dft<T, R, 1>::run(x[q]);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                C2<T> a[Ch::N];
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) a[q] = j == 0 ? x[q][0] : cmul(x[q][j], tf[j - 1]);
+                *reinterpret_cast<V *>(lb + j * sb) = Ch::join(a);
+            }
+        });
+    }
+    __syncthreads();
+    // and step one: slots -> registers -> rows
+    for (int it = threadIdx.x; it < C * R2; it += nt) {
+        const int p = it / C, c = it - p * C, w = c / kCpc, q0 = c - w * kCpc;
+        V *g = reinterpret_cast<V *>((w ? col1 : col0) + (size_t)p * plane) + q0;
+        const unsigned char *lb = buf + p * sb + c * 16;
+        const size_t step = (size_t)R2 * plane * sizeof(C2<T>);
+        with_radix<RMAX>(R1, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<T> x[Ch::N][R];
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                C2<T> a[Ch::N];
+                Ch::split(*reinterpret_cast<const V *>(lb + k * s1), a);
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) x[q][k] = a[q];
+            }
+#pragma unroll
+            for (int q = 0; q < Ch::N; ++q) Dft<T, R, 1>::run(x[q]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                C2<T> a[Ch::N];
+#pragma unroll
+                for (int q = 0; q < Ch::N; ++q) a[q] = x[q][r];
+                gst(reinterpret_cast<V *>(reinterpret_cast<char *>(g) + r * step))[0] = Ch::join(a);
+            }
+        });
+    }
+    const double sum = block_sum_n(e);
     if (threadIdx.x == 0) I.part_ek[t.slot] = sum;
 }
 
@@ -1270,7 +1394,7 @@ static void allow_lds(K kernel, size_t bytes) {
 #define VDWNL_LAUNCH(kern, ...)                                                                      \
     do {                                                                                             \
         if (a.ntiles == 0) allow_lds(kern, a.lds);                                                   \
-        else hipLaunchKernelGGL(kern, dim3(a.ntiles), dim3(kThreads), a.lds, a.stream, a.insts, a.tiles, \
+        else hipLaunchKernelGGL(kern, dim3(a.ntiles), dim3(a.threads), a.lds, a.stream, a.insts, a.tiles, \
                                 __VA_ARGS__);                                                        \
     } while (0)
 
@@ -1293,39 +1417,50 @@ hipError_t launch_y_lc(int kind, const LaunchArgs &a) {
     switch (kind) {
         case KG_Y: VDWNL_LAUNCH((k_dcol<T, double, LC, V, 0, 2>), a.twd); break;
         case KD_Y: VDWNL_LAUNCH((k_dcol<T, T, LC, V, 1, 2>), a.tw); break;
-        case KY_20F: VDWNL_LAUNCH((k_y<T, -1, LC, V>), a.tw); break;
-        case KY_20I: VDWNL_LAUNCH((k_y<T, 1, LC, V>), a.tw); break;
         default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// the axis-2 passes of the 20 spectra: by split class
+template <typename T, int S>
+hipError_t launch_y20(int cls, const LaunchArgs &a) {
+    switch (cls) {
+        case 0: VDWNL_LAUNCH((k_y<T, S, kSplitClassMax[0]>), a.tw); break;
+        case 1: VDWNL_LAUNCH((k_y<T, S, kSplitClassMax[1]>), a.tw); break;
+        case 2: VDWNL_LAUNCH((k_y<T, S, kSplitClassMax[2]>), a.tw); break;
+        default: VDWNL_LAUNCH((k_y_any<T, S>), a.tw); break;
     }
     return hipGetLastError();
 }
 
 template <typename T, int LC, int V>
 hipError_t launch_z_lc(int kind, const LaunchArgs &a) {
-    constexpr bool F32 = sizeof(T) == 4;
     switch (kind) {
         case KG_Z: VDWNL_LAUNCH((k_dcol<T, double, LC, V, 0, 1>), a.twd); break;
         case KD_Z: VDWNL_LAUNCH((k_dcol<T, T, LC, V, 1, 1>), a.tw); break;
-        case KZ_MAIN:
-            if (a.general && a.packed) VDWNL_LAUNCH((k_z_main<T, LC, V, true, 0, false, true>), a.cols, a.tw);
-            else if (a.general) VDWNL_LAUNCH((k_z_main<T, LC, V, true, 0, false, false>), a.cols, a.tw);
-            else if (F32 && a.mfma) VDWNL_LAUNCH((k_z_main<T, LC, V, false, 0, F32, false>), a.cols, a.tw);
-            else VDWNL_LAUNCH((k_z_main<T, LC, V, false, 0, false, false>), a.cols, a.tw);
-            break;
-        case KP_THETA_K:
-            // (the forward spectra alone: no kernel rows read)
-            if (a.general) VDWNL_LAUNCH((k_z_main<T, LC, V, true, 1, false, false>), a.cols, a.tw);
-            else VDWNL_LAUNCH((k_z_main<T, LC, V, false, 1, false, false>), a.cols, a.tw);
-            break;
-        case KP_U_K:
-            if (a.general && a.packed) VDWNL_LAUNCH((k_z_main<T, LC, V, true, 2, false, true>), a.cols, a.tw);
-            else if (a.general) VDWNL_LAUNCH((k_z_main<T, LC, V, true, 2, false, false>), a.cols, a.tw);
-            else if (F32 && a.mfma) VDWNL_LAUNCH((k_z_main<T, LC, V, false, 2, F32, false>), a.cols, a.tw);
-            else VDWNL_LAUNCH((k_z_main<T, LC, V, false, 2, false, false>), a.cols, a.tw);
-            break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+// the fused axis-1 pass and its probes: by split class (N1 <= 204: radices to 25)
+template <typename T, int CT>
+hipError_t launch_zmain(int cls, int probe, const LaunchArgs &a) {
+    switch (cls) {
+        case 0: VDWNL_LAUNCH((k_z_main<T, CT, kZClassMax[0]>), a.cols, a.tw, probe); break;
+        case 1: VDWNL_LAUNCH((k_z_main<T, CT, kZClassMax[1]>), a.cols, a.tw, probe); break;
+        case 2: VDWNL_LAUNCH((k_z_main<T, CT, kZClassMax[2]>), a.cols, a.tw, probe); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_zmain(int cls, int probe, const LaunchArgs &a) {
+    if (a.general) return a.packed ? launch_zmain<T, CT_GEN_PACKED>(cls, probe, a) : launch_zmain<T, CT_GEN>(cls, probe, a);
+    if constexpr (sizeof(T) == 4)
+        if (a.mfma) return launch_zmain<T, CT_MFMA>(cls, probe, a);
+    return launch_zmain<T, CT_VEC>(cls, probe, a);
 }
 
 #undef VDWNL_LAUNCH

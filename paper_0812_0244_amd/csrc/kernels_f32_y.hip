@@ -5,6 +5,8 @@
 namespace vdwnl {
 
 hipError_t launch_y_f32(int kind, int lc, int var, const LaunchArgs &a) {
+    if (kind == KY_20F) return launch_y20<float, -1>(lc, a);
+    if (kind == KY_20I) return launch_y20<float, 1>(lc, a);
     VDWNL_LC_VARIANTS(launch_y_lc, float, kind, lc, var, a)
 }
 

@@ -5,6 +5,8 @@
 namespace vdwnl {
 
 hipError_t launch_y_f64(int kind, int lc, int var, const LaunchArgs &a) {
+    if (kind == KY_20F) return launch_y20<double, -1>(lc, a);
+    if (kind == KY_20I) return launch_y20<double, 1>(lc, a);
     VDWNL_LC_VARIANTS(launch_y_lc, double, kind, lc, var, a)
 }
 
