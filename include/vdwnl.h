@@ -277,8 +277,10 @@ int vdwnl_log_qmesh(int32_t nq, double q1, double q_c, double lambda, double *q_
  * timed evaluations into *calls, and returns the number of entries.
  * vdwnl_pass_name(k) names kind k ("" outside the range); vdwnl_pass_order
  * writes the kinds the planned mode launches, in launch order, into kinds[]
- * (at most max_passes) and returns their number.  Timed evaluations launch
- * their passes one by one (no graph). */
+ * (at most max_passes) and returns their number.  Passes that run in another's
+ * launch show there: the gradient's directions (all in x_deriv in
+ * orthorhombic cells) and the energy reduction (in y_20i).  Timed evaluations
+ * launch their passes one by one (no graph). */
 int vdwnl_set_timing(vdwnl_ctx *ctx, int32_t on);
 int vdwnl_pass_times(const vdwnl_ctx *ctx, int32_t max_passes, double *ms, int64_t *calls);
 const char *vdwnl_pass_name(int32_t i);
@@ -291,14 +293,12 @@ int vdwnl_set_graph(vdwnl_ctx *ctx, int32_t on);
 /* Schedule tuning for the planned grids: evaluates the batch (n_ptrs[nb],
  * v_ptrs[nb] as for vdwnl_energy_potential_batched; v is overwritten) once
  * plus `reps` timed times (1..100) for each candidate LDS budget (and, for
- * FP32 orthorhombic grids, each contraction unit) at radix order 0, the first
+ * FP32 orthorhombic grids, each contraction unit), the first
  * candidate after some 300 ms of untimed evaluations so that the device's
- * clocks have risen before any timing, keeps
- * the unit of the fused axis-1 pass with the least time over that pass, then
- * times every candidate budget at every radix order (0..5) with that unit and
- * picks per pass group the (budget, order) pair with the least time over the
- * group's passes, plans with the choices and remembers them, keyed by the device
- * architecture, its LDS size,
+ * clocks have risen before any timing, keeps per pass group the budget (for
+ * the fused axis-1 pass, the budget and unit) with the least time over the
+ * group's passes, plans with the choices and remembers them, keyed by the
+ * device architecture, its LDS size,
  * the precision, the gradient mode and the exact grid list: for the rest of
  * the process, and in the tuning file for later processes.  The file is a
  * JSON object with one entry per line, "<arch>/<key hash>": [five budgets,
@@ -320,10 +320,12 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
  *     or VDWNL_CONTRACTION_MATRIX (the matrix cores: 16-block 4 x 4 x 1 FP32
  *     outer products, 15 blocks per instruction for the 20 x 20 matrices of
  *     three k-point groups); FP64 and general cells always use the vector ALU.
- *   VDWNL_SCHEDULE_RADIX_*  the radix order of a pass group's transforms.
- * vdwnl_autotune chooses the contraction unit together with the LDS budgets,
- * then the radix orders (and a plan reuses tuned choices as it does the
- * budgets); untuned, the matrix cores and order 0.  Setting a choice
+ *   VDWNL_SCHEDULE_RADIX_*  a radix order of a pass group's transforms
+ *     (vdwnl_radix_order lists them).  Kept and reported, without effect: every
+ *     transform runs as its length's most even split into two radices.
+ * vdwnl_autotune chooses the contraction unit together with the LDS budgets
+ * (and a plan reuses tuned choices as it does the budgets); untuned, the
+ * matrix cores and order 0.  Setting a choice
  * re-plans the launches (the workspace is rebuilt at the next evaluation).
  * VDWNL_E_ARG for an unknown choice or value; VDWNL_E_STATE without a planned
  * grid. */
@@ -344,8 +346,8 @@ enum { VDWNL_CONTRACTION_VECTOR = 0, VDWNL_CONTRACTION_MATRIX = 1 };
 int vdwnl_set_schedule(vdwnl_ctx *ctx, int32_t what, int32_t value);
 int vdwnl_get_schedule(const vdwnl_ctx *ctx, int32_t what, int32_t *value);
 
-/* The radix passes (each 2, 3, 4, 5, 8 or 16, in order) of the transform of
- * length n in radix order `order` (0..5; a larger order than the length has
+/* The radices (each 2, 3, 4, 5, 8 or 16, in order) that make up length n in
+ * radix order `order` (0..5; a larger order than the length has
  * takes its last): up to max_radices values into radices[] (host array).
  * Returns their number, VDWNL_E_ARG for bad arguments, or
  * VDWNL_E_UNSUPPORTED_SIZE for a length with a prime factor above 5.  Host

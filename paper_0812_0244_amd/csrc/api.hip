@@ -32,6 +32,9 @@ static bool radix_plan(int n, FftPlan &p) {
     while (m % 5 == 0) { p.radix[p.nstage++] = 5; m /= 5; }
     while (m % 3 == 0) { p.radix[p.nstage++] = 3; m /= 3; }
     (void)split_radices(n, p.r1, p.r2);
+    p.d1 = div_magic(p.r1);
+    p.d2 = div_magic(p.r2);
+    p.dn = div_magic(n);
     return m == 1 && p.nstage <= kMaxStages;
 }
 
@@ -131,19 +134,6 @@ constexpr int kDefaultContraction = VDWNL_CONTRACTION_MATRIX;
 // Pass groups whose tile shapes follow one LDS budget each.
 enum TileGroup { TG_X = 0, TG_Y20, TG_YAUX, TG_Z, TG_ZAUX, TG_COUNT };
 
-// The pass group whose radix order a pass takes: every axis-3 transform, the
-// axis-2 transforms of the 20 spectra, the other axis-2 transforms (the
-// gradient and divergence), the fused axis-1 pass, the other axis-1 passes.
-static int variant_group(int kind) {
-    switch (kind) {
-        case KY_20F: case KY_20I: return TG_Y20;
-        case KG_Y: case KD_Y: return TG_YAUX;
-        case KZ_MAIN: return TG_Z;
-        case KG_Z: case KD_Z: return TG_ZAUX;
-        default: return TG_X;
-    }
-}
-
 struct Grid {
     int s[3];
     double A[3][3];          // cell vectors a_c (rows, bohr)
@@ -152,10 +142,10 @@ struct Grid {
     double cell[3];          // |a_c| (the orthorhombic lengths when !general)
     FftPlan p1, p2, p3;
     int bmain;               // rows per theta / assemble tile
-    int bnf;                 // rows per axis-3 derivative tile (and stencil tile; even)
+    int bnf;                 // rows per stencil tile
     int k3main;              // columns per fused axis-1 tile (1 or 2)
     int wy20;                // axis-2 tile width of the 20 spectra
-    int wdy, wdz;            // i3 per axis-2 / axis-1 derivative tile
+    int wdy;                 // i3 per axis-2 derivative tile with run-time radices
     int shell_key;           // index into Ctx::shells
     size_t off_grad, off_vloc, off_spec, off_map, off_tab, off_ek, off_de, off_sl, off_bad;
     int n_ek, n_de;
@@ -209,7 +199,7 @@ struct vdwnl_ctx {
     std::string err;
     size_t pref[TG_COUNT] = {kLdsCap, kLdsCap, kLdsCap, kLdsCap, kLdsCap};   // LDS budget per pass group
     int contraction = VDWNL_CONTRACTION_VECTOR;   // unit of the per-k contraction (FP32, orthorhombic)
-    int variant[TG_COUNT] = {0, 0, 0, 0, 0};        // radix order per pass group
+    int variant[TG_COUNT] = {0, 0, 0, 0, 0};        // radix order per pass group (listed, no effect)
     std::string plan_key;                 // identifies the batch for the tuned-budget cache
     std::string arch = "host";            // device architecture (gcnArchName)
     // plan
@@ -247,9 +237,9 @@ struct vdwnl_ctx {
         int group = 0;
         int general = 0;      // grids of the group in non-orthogonal cells
         int mfma = 0;         // (fused axis-1 pass) the contraction on the matrix cores
-        int var = 0;          // radix order of the transform (its length class's variant)
         int packed = 0;       // (general cells) shell tables of packed upper triangles
         int threads = 0;      // per workgroup
+        int len = 0;          // (axis-3 passes) the length, where it has a compile-time kernel
     };
     // per pass: one launch per group of grids (grids whose three axes fall in
     // the same FFT length classes); the groups' chains of passes are
@@ -405,19 +395,40 @@ static bool smooth235(int n) {
     return n == 1;
 }
 
-// LDS of one theta / assembly tile of b rows: the 20 fields' pair lines,
-// twiddles and method constants.
-static size_t xpass_lds(size_t b, size_t N3, size_t rs) {
-    const size_t cs = 2 * rs;
-    return b * (N3 + 1) * (kNQ / 2) * cs + N3 * cs + (kNQ + kNQ * kNQ) * rs + (kMaxMc + 1) * 8;
+// LDS of one theta / assembly tile of b rows: the rows' pair values as the
+// kernels pitch them, the twiddles, the method constants, the slots of the
+// frequencies.
+static size_t xpass_lds(const Grid &g, size_t b, size_t rs) {
+    const int eb = kNQ * (int)rs, r2 = g.p3.r2;
+    const size_t gs = (size_t)r2 * eb + (((1 - r2) * eb) & 255);
+    return b * g.p3.r1 * gs + g.s[2] * (2 * rs + sizeof(int)) + (kNQ + kNQ * kNQ + kMaxMc + 1) * rs;
 }
 
-// LDS of one derivative tile of a one-axis pass: twiddles and np lines of
-// length L, complex elements of ce bytes (16: the gradient's FP64, or the
-// working precision's for the divergence); lines at pitch L | 1 along axes
-// 2 and 1, at pitch N3 + 1 along axis 3 (the rows).
+// Rows of an axis-3 tile and its threads: a point each, in whole waves with
+// few idle lanes among 128 to 256 threads: the most threads (128^3 and 64^3 in
+// FP32, theta pass of batches: 222 and 112 us with 256, 235 and 120 with 128),
+// or the fewest while the grid gives a CU less than two tiles; longer rows
+// stand alone.
+static int xpass_rows(const Grid &g, size_t rs, size_t budget) {
+    const int n3 = g.s[2], rows = g.s[0] * g.s[1];
+    int best = 1;
+    double eff = 0.0;
+    for (int b = 1; b == 1 || (b * n3 <= kMaxThreads && b <= rows); ++b) {
+        if (b > 1 && xpass_lds(g, b, rs) > budget) break;
+        const int nt = std::max(128, (b * n3 + 63) / 64 * 64);
+        const double e = (double)b * n3 / nt;
+        if (e > eff + (rows / b >= 512 ? -0.03 : 0.04)) { eff = std::max(e, eff); best = b; }
+    }
+    return best;
+}
+static int xpass_threads(const Grid &g) {
+    return std::min(std::max(128, (g.bmain * g.s[2] + 63) / 64 * 64), kMaxThreads);
+}
+
+// LDS of one derivative tile of a one-axis pass with run-time radices:
+// twiddles and np lines of length L, complex elements of ce bytes (16: the
+// gradient's FP64, or the working precision's for the divergence).
 static size_t deriv_lds(size_t L, size_t np, size_t ce) { return (L + np * (L | 1)) * ce; }
-static size_t drow_lds(size_t N3, size_t np, size_t ce) { return (N3 + np * (N3 + 1)) * ce; }
 
 // lattice: 9 values, rows a_1, a_2, a_3 (bohr)
 static int check_grid(vdwnl_ctx *c, const int32_t *shape, const double *lattice, int precision, Grid &g) {
@@ -459,7 +470,7 @@ static int check_grid(vdwnl_ctx *c, const int32_t *shape, const double *lattice,
         return fail(c, VDWNL_E_UNSUPPORTED_SIZE, "more than 715827882 grid points");
     // LDS of each pass as a function of its tile size (twiddles staged in LDS too)
     auto zmain = [&](size_t k3) { return (N1 + kNQ * k3 * (N1 | 1)) * cs + 16 + (N1 / 2 + 1) * k3 * sizeof(int); };
-    auto xmain = [&](size_t b) { return xpass_lds(b, N3, rs); };
+    auto xmain = [&](size_t b) { return b * (N3 + 1) * (kNQ / 2) * cs + N3 * cs + (kNQ + kNQ * kNQ) * rs + (kMaxMc + 1) * 8; };
     auto ypass = [&](size_t w, size_t c2) { return (N2 + (N2 | 1) * w) * c2; };
     const size_t cap = c->lds_cap;
     if (N1 > (size_t)kMaxN1 || zmain(1) > cap || deriv_lds(N1, 1, 16) > cap)
@@ -473,11 +484,19 @@ static int check_grid(vdwnl_ctx *c, const int32_t *shape, const double *lattice,
     return VDWNL_OK;
 }
 
-// Split class of the axis-2 passes of the 20 spectra (kLenGeneric: the
-// run-time radix passes; also where a tile's lines would exceed the LDS).
-static int y20_class(const vdwnl_ctx *c, const Grid &g) {
-    return (size_t)g.s[1] * kYC * 16 <= c->lds_cap ? split_class(g.s[1]) : kLenGeneric;
+// LDS of an axis-2 tile of the 20 spectra (lengths that split; the lanes of
+// its class).
+static int y_lanes(const Grid &g) { return tile_lanes(kSplitClassMax[std::min(split_class(g.s[1]), kNumSplitClasses - 1)]); }
+static size_t y_lds(const Grid &g) { return ((size_t)g.s[1] * 16) << y_lanes(g); }
+
+// Split class of the axis-2 passes (kLenGeneric: the run-time radix passes;
+// also where a tile's lines would exceed the LDS).
+static int y_class(const vdwnl_ctx *c, const Grid &g) {
+    return y_lds(g) <= c->lds_cap ? split_class(g.s[1]) : kLenGeneric;
 }
+
+// LDS of an axis-3 derivative tile, as the kernel pitches its slots.
+static size_t drow_lds(const Grid &g, size_t ce) { return ((size_t)g.p3.r1 * (g.p3.r2 | 1) * ce) << tile_lanes(g.p3.r2); }
 
 // LDS of a fused axis-1 tile of K columns: R1 runs of R2 slots (each run
 // padded as the kernel pads it), the slot of every frequency and the shell of
@@ -489,11 +508,10 @@ static size_t zmain_lds(const Grid &g, int K, size_t cs) {
 }
 
 // Threads of a fused axis-1 workgroup: an item of the wider step each (a
-// chunk of a column and one of R2 residues), at most what the kernel is
-// compiled for.
+// chunk of a column and one of R2 residues), up to four waves.
 static int zmain_threads(const Grid &g, int K, size_t cs) {
     const int items = K * kNQ * (int)cs / 16 * g.p1.r2;
-    return std::min((items + 63) / 64 * 64, 512);
+    return std::min((items + 63) / 64 * 64, kMaxThreads);
 }
 
 // Tile shapes of grid g from the LDS budget of each pass group: each tile as
@@ -501,23 +519,14 @@ static int zmain_threads(const Grid &g, int K, size_t cs) {
 static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     const size_t cs = c->precision == 64 ? 16 : 8, rs = c->precision == 64 ? 8 : 4;
     const size_t N1 = g.s[0], N2 = g.s[1], N3 = g.s[2];
-    auto xmain = [&](size_t b) { return xpass_lds(b, N3, rs); };
     auto ypass = [&](size_t w, size_t c2) { return (N2 + (N2 | 1) * w) * c2; };
-    // complex elements per LDS FFT tile: bounded for the runtime-radix FFT
-    // (its per-thread register arrays), not for the compile-time plans
-    auto cap = [](size_t n) { return len_class((int)n) == kLenGeneric ? (size_t)kTileCap : (size_t)1 << 30; };
-    // axis-3 tiles of the theta / assembly passes: at most one grid point
-    // per thread (two measured slower: the local chain needs the VGPRs);
-    // of the derivative passes (FP64 lines, one per row pair): about 4096
-    // points, enough lines to occupy every lane
-    g.bmain = 1;
-    while ((size_t)(g.bmain + 1) * N3 <= (size_t)kThreads && (kNQ / 2) * (g.bmain + 1) * N3 <= cap(N3) &&
-           xmain(g.bmain + 1) <= c->pref[TG_X])
-        ++g.bmain;
+    // complex elements per LDS tile of the run-time radix passes (axis-2
+    // lengths without a split), bounded by their per-thread register arrays
+    auto cap = [](size_t) { return (size_t)kTileCap; };
+    g.bmain = xpass_rows(g, rs, c->pref[TG_X]);
+    // rows of a stencil tile: about 4096 points
     g.bnf = 2;
-    while ((size_t)(g.bnf + 2) * N3 <= 4096 && (size_t)(g.bnf / 2 + 1) * N3 <= cap(N3) &&
-           drow_lds(N3, g.bnf / 2 + 1, 16) <= kLdsCap)
-        g.bnf += 2;
+    while ((size_t)(g.bnf + 2) * N3 <= 4096) g.bnf += 2;
     // fused axis-1 tiles: two columns (a pair k2, N2 - k2 shares its kernel
     // rows) where they fit the budget; in FP64, whose columns are twice as
     // large, only up to 16 KB: a second workgroup per CU is worth more than the
@@ -528,8 +537,8 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     g.wy20 = 1;
     while ((size_t)(g.wy20 + 1) * N2 <= cap(N2) && ypass(g.wy20 + 1, cs) <= c->pref[TG_Y20]) ++g.wy20;
     if (g.wy20 > 1) g.wy20 &= ~1;   // even widths: 16-byte aligned FP32 rows
-    // derivative tiles along axes 2 and 1: i3 columns in pairs (one FP64
-    // line each), within the group's budget
+    // derivative tiles along an axis 2 with run-time radices: i3 columns in
+    // pairs (one FP64 line each), within the group's budget
     // (a width short of the whole row: a multiple of 32 once it reaches 32,
     // so that the runs of i3 start and end on 128-byte boundaries)
     auto dwidth = [&](size_t L, size_t budget) {
@@ -541,7 +550,6 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
         return w;
     };
     g.wdy = dwidth(N2, c->pref[TG_YAUX]);
-    g.wdz = dwidth(N1, c->pref[TG_ZAUX]);
 }
 
 // Tuned LDS budgets, keyed by the device architecture, LDS size, precision,
@@ -818,20 +826,6 @@ static void xcd_blocks(std::vector<Tile> &t) {
     t.swap(out);
 }
 
-// The pass whose tile list a pass takes: its own, or that of the pass that
-// walks the same tiles in the other direction.
-static int tile_kind(int kind) {
-    switch (kind) {
-        case KY_20I: return KY_20F;
-        case KX_ASSEMBLE: return KX_THETA;
-        case KD_X: return KG_X;
-        case KD_Y: return KG_Y;
-        case KD_Z: return KG_Z;
-        case KF_DIV: return KF_GRAD;
-        default: return kind;
-    }
-}
-
 static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
     const bool dp = c->precision == 64;
     const size_t rs = dp ? 8 : 4, cs = 2 * rs;
@@ -855,11 +849,18 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
         const int inst = (int)gi;
         size_t first_tile[KIND_COUNT];
         for (int k = 0; k < KIND_COUNT; ++k) first_tile[k] = tiles[k].size();
-        // axis-3 tiles (and the stencil passes' runs of lines)
-        const bool fd = c->grad_mode > 0;
-        for (int r = 0; r < rows; r += g.bnf) {
-            const int b = std::min(g.bnf, rows - r);   // even: rows and bnf are
-            tiles[fd ? KF_GRAD : KG_X].push_back({inst, r, b, 0, -1});
+        // runs of lines of the stencil passes; or the tiles of the one-axis
+        // derivatives (slot = the axis)
+        if (c->grad_mode > 0) {
+            for (int r = 0; r < rows; r += g.bnf) tiles[KF_GRAD].push_back({inst, r, std::min(g.bnf, rows - r), 0, -1});
+        } else {
+            const int w1 = 2 << tile_lanes(g.p1.r2), w3 = 2 << tile_lanes(g.p3.r2);
+            const int w2 = y_class(c, g) != kLenGeneric ? 2 << tile_lanes(g.p2.r2) : g.wdy;
+            for (int i1 = 0; i1 < N1; ++i1)
+                for (int i3 = 0; i3 < N3; i3 += w2) tiles[KD_Y].push_back({inst, i1, i3, std::min(w2, N3 - i3), 2});
+            for (int r = 0; r < rows; r += w3) tiles[KD_X].push_back({inst, r, std::min(w3, rows - r), 0, 3});   // (rows: even)
+            for (int i2 = 0; i2 < N2; ++i2)
+                for (int i3 = 0; i3 < N3; i3 += w1) tiles[KD_Z].push_back({inst, i2, i3, std::min(w1, N3 - i3), 1});
         }
         int slot = 0;
         for (int r = 0; r < rows; r += g.bmain) {
@@ -867,20 +868,13 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
             tiles[KX_THETA].push_back({inst, r, b, 0, slot++});
         }
         g.n_de = slot;
-        // axis-2 tiles of the 20 spectra: runs of kYC 16-byte chunks, or (no
+        // axis-2 tiles of the 20 spectra: runs of 16-byte chunks, or (no
         // split) of wy20 complex values
         {
-            const bool split = y20_class(c, g) != kLenGeneric;
-            const int len = split ? N3h * kNQ / (int)(16 / cs) : N3h * kNQ, w = split ? kYC : g.wy20;
+            const bool split = y_class(c, g) != kLenGeneric;
+            const int len = split ? N3h * kNQ / (int)(16 / cs) : N3h * kNQ, w = split ? 1 << y_lanes(g) : g.wy20;
             for (int i1 = 0; i1 < N1; ++i1)
                 for (int f = 0; f < len; f += w) tiles[KY_20F].push_back({inst, i1, f, std::min(w, len - f), -1});
-        }
-        // derivative tiles along axes 2 (a = i1) and 1 (a = i2): runs of i3
-        if (!fd) {
-            for (int i1 = 0; i1 < N1; ++i1)
-                for (int i3 = 0; i3 < N3; i3 += g.wdy) tiles[KG_Y].push_back({inst, i1, i3, std::min(g.wdy, N3 - i3), -1});
-            for (int i2 = 0; i2 < N2; ++i2)
-                for (int i3 = 0; i3 < N3; i3 += g.wdz) tiles[KG_Z].push_back({inst, i2, i3, std::min(g.wdz, N3 - i3), -1});
         }
         // Fused axis-1 tiles: the columns k2 and N2 - k2 (the same |m2|, so
         // the same |G| shell at every (|m1|, k3)) over a run of consecutive
@@ -936,29 +930,36 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
         const size_t N1 = g.s[0], N2 = g.s[1], N3 = g.s[2];
         switch (k) {
             // the gradient's derivatives in FP64, the divergence's in the working precision
-            case KG_X: return drow_lds(N3, g.bnf / 2, 16);
-            case KD_X: return drow_lds(N3, g.bnf / 2, cs);
-            case KG_Y: return deriv_lds(N2, (g.wdy + 1) / 2, 16);
-            case KD_Y: return deriv_lds(N2, (g.wdy + 1) / 2, cs);
-            case KG_Z: return deriv_lds(N1, (g.wdz + 1) / 2, 16);
-            case KD_Z: return deriv_lds(N1, (g.wdz + 1) / 2, cs);
+            case KD_X: return drow_lds(g, cs);
+            case KD_Y: return y_class(c, g) != kLenGeneric ? (N2 * cs) << tile_lanes(g.p2.r2) : deriv_lds(N2, (g.wdy + 1) / 2, cs);
+            case KD_Z: return (N1 * cs) << tile_lanes(g.p1.r2);
+            case KG_X: return drow_lds(g, 16);
+            case KG_Y: return y_class(c, g) != kLenGeneric ? (N2 * 16) << tile_lanes(g.p2.r2) : deriv_lds(N2, (g.wdy + 1) / 2, 16);
+            case KG_Z: return (N1 * 16) << tile_lanes(g.p1.r2);
             case KF_GRAD: case KF_DIV: return 0;
-            case KX_THETA: case KX_ASSEMBLE: return xpass_lds(g.bmain, N3, rs);
+            case KX_THETA: case KX_ASSEMBLE: return xpass_lds(g, g.bmain, rs);
             case KY_20F: case KY_20I:
-                return y20_class(c, g) != kLenGeneric ? N2 * kYC * 16 : (N2 + (N2 | 1) * g.wy20) * cs;
+                return std::max(k == KY_20I ? kReduceLds : 0,
+                                y_class(c, g) != kLenGeneric ? y_lds(g) : (N2 + (N2 | 1) * g.wy20) * cs);
             default: return zmain_lds(g, g.k3main, cs);   // KZ_MAIN
         }
     };
-    // the axis whose FFT a pass performs: 3 for the axis-3 passes, 2, 1
-    auto axis_len = [&](int k, const Grid &g) -> int {
+    // threads of a workgroup of each pass for grid g: an item of the wider
+    // transform step each
+    auto threads_of = [&](int k, const Grid &g) -> int {
+        auto lanes = [](int n) { return (n + 63) / 64 * 64; };
         switch (k) {
-            case KG_X: case KD_X: case KX_THETA: case KX_ASSEMBLE: return g.s[2];
-            case KG_Y: case KD_Y: case KY_20F: case KY_20I: return g.s[1];
-            default: return g.s[0];
+            case KG_X: case KD_X: return lanes(g.p3.r2 << tile_lanes(g.p3.r2));
+            case KG_Y: case KD_Y: return y_class(c, g) != kLenGeneric ? lanes(g.p2.r2 << tile_lanes(g.p2.r2)) : kThreads;
+            case KG_Z: case KD_Z: return lanes(g.p1.r2 << tile_lanes(g.p1.r2));
+            case KY_20F: case KY_20I: return y_class(c, g) != kLenGeneric ? lanes(g.p2.r2 << y_lanes(g)) : kThreads;
+            case KZ_MAIN: return zmain_threads(g, g.k3main, cs);
+            case KX_THETA: case KX_ASSEMBLE: return xpass_threads(g);
+            default: return kThreads;
         }
     };
-    // groups: grids with the same length classes on all three axes (every
-    // pass of a group is then one launch).  (Dealing a group with a large
+    // groups: grids of the same classes on all three axes (every pass of a
+    // group is then one launch).  (Dealing a group with a large
     // share of the points into sub-groups measured no faster.)
     std::vector<int> group_of(c->grids.size());
     {
@@ -967,8 +968,9 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
             const Grid &g = c->grids[gi];
             // (and the cell kind and kernel-row layout: general cells take the
             // fused pass's general variant, full or packed rows)
-            const int key = ((len_class(g.s[0]) * kNumLenClasses + len_class(g.s[1])) * kNumLenClasses +
-                             len_class(g.s[2])) * 16 + std::min(y20_class(c, g), 3) * 4 + (g.general ? 1 : 0) + (c->shells[g.shell_key].packed ? 2 : 0);
+            const int cls = (std::min(split_class(g.s[0]), 4) * 5 + std::min(y_class(c, g), 4)) * 5 + split_class(g.s[2]);
+            // (lengths of axis 3 with a compile-time kernel: groups of their own)
+            const int key = (cls * kNumLenClasses + len_class(g.s[2])) * 4 + (g.general ? 1 : 0) + (c->shells[g.shell_key].packed ? 2 : 0);
             auto it = std::find(keys.begin(), keys.end(), key);
             group_of[gi] = (int)(it - keys.begin());
             if (it == keys.end()) keys.push_back(key);
@@ -1003,47 +1005,82 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
         }
         tiles[KZ_MAIN].swap(out);
     }
+    // The launches, and the tile list they index: per group and pass the
+    // tiles in a run; the three derivative directions of a group in one run
+    // (axis 2, 3, 1), since the gradient takes several of them in one launch.
     std::vector<Tile> all;
+    for (int k = 0; k < KIND_COUNT; ++k) c->launches[k].clear();
     {
-        std::vector<std::vector<Tile>> mine(c->ngroups);
-        std::vector<int> first(c->ngroups, 0), count(c->ngroups, 0);
-        for (int k = 0; k < KIND_COUNT; ++k) c->launches[k].clear();
-        for (int base = 0; base < KIND_COUNT; ++base) {
-            if (tile_kind(base) != base || tiles[base].empty()) continue;
-            for (const Tile &tl : tiles[base]) mine[group_of[tl.inst]].push_back(tl);
-            for (int grp = 0; grp < c->ngroups; ++grp) {
-                first[grp] = (int)all.size();
-                count[grp] = (int)mine[grp].size();
-                all.insert(all.end(), mine[grp].begin(), mine[grp].end());
-                mine[grp].clear();
+        std::vector<std::vector<Tile>> mine[KIND_COUNT];
+        for (int k = 0; k < KIND_COUNT; ++k) {
+            mine[k].resize(c->ngroups);
+            for (const Tile &tl : tiles[k]) mine[k][group_of[tl.inst]].push_back(tl);
+        }
+        for (int grp = 0; grp < c->ngroups; ++grp) {
+            int off[KIND_COUNT], cnt[KIND_COUNT];
+            int ng = 0;       // the energy reductions, first of the inverse axis-2 pass
+            for (int k : {KD_Y, KD_X, KD_Z, KX_THETA, KY_20F, KZ_MAIN, KF_GRAD}) {
+                if (k == KY_20F)
+                    for (size_t gi = 0; gi < c->grids.size(); ++gi)
+                        if (group_of[gi] == grp) {
+                            all.push_back({(int)gi, -1, 0, 0, -1});
+                            ++ng;
+                        }
+                off[k] = (int)all.size();
+                cnt[k] = (int)mine[k][grp].size();
+                all.insert(all.end(), mine[k][grp].begin(), mine[k][grp].end());
             }
-            for (int k = base; k < KIND_COUNT; ++k) {
-                if (tile_kind(k) != base) continue;
-                std::vector<vdwnl_ctx::Launch> ls(c->ngroups);
-                for (size_t gi = 0; gi < c->grids.size(); ++gi) {
-                    const Grid &g = c->grids[gi];
-                    const bool plain = k == KF_GRAD || k == KF_DIV, y20 = k == KY_20F || k == KY_20I;
-                    vdwnl_ctx::Launch &L = ls[group_of[gi]];
-                    L.general = g.general ? 1 : 0;
-                    L.packed = c->shells[g.shell_key].packed ? 1 : 0;
-                    L.mfma = (k == KZ_MAIN && c->precision == 32 && !g.general &&
-                              c->contraction == VDWNL_CONTRACTION_MATRIX) ? 1 : 0;
-                    // the stencil passes transform nothing (class 0 for any grid)
-                    L.lc = plain ? 0 : y20 ? y20_class(c, g) : k == KZ_MAIN ? split_class(g.s[0]) : len_class(axis_len(k, g));
-                    L.var = (plain || y20 || k == KZ_MAIN) ? 0 : std::min(c->variant[variant_group(k)], kNumVariants[L.lc] - 1);
-                    L.threads = std::max(L.threads, k == KZ_MAIN ? zmain_threads(g, g.k3main, cs)
-                                                    : y20 && L.lc != kLenGeneric ? (kYC * g.p2.r2 + 63) / 64 * 64 : kThreads);
-                    L.lds = std::max(L.lds, lds_of(k, g));
+            const Grid &g0 = c->grids[std::find(group_of.begin(), group_of.end(), grp) - group_of.begin()];
+            // one launch of pass k over cnt tiles from off; lds and threads: the
+            // largest any grid needs in one of the passes `as`
+            auto add = [&](int k, int o, int n, int cls, std::initializer_list<int> as) {
+                if (n == 0) return;
+                vdwnl_ctx::Launch L;
+                L.kind = k;
+                L.lc = cls;
+                L.off = o;
+                L.cnt = n;
+                L.group = grp;
+                L.general = g0.general ? 1 : 0;
+                L.len = len_class(g0.s[2]) != kLenGeneric ? g0.s[2] : 0;
+                L.packed = c->shells[g0.shell_key].packed ? 1 : 0;
+                L.mfma = (k == KZ_MAIN && !dp && !g0.general && c->contraction == VDWNL_CONTRACTION_MATRIX) ? 1 : 0;
+                for (size_t gi = 0; gi < c->grids.size(); ++gi)
+                    for (int q : as)
+                        if (group_of[gi] == grp) {
+                            L.lds = std::max(L.lds, lds_of(q, c->grids[gi]));
+                            L.threads = std::max(L.threads, threads_of(q, c->grids[gi]));
+                        }
+                c->launches[k].push_back(L);
+            };
+            const int c1 = split_class(g0.s[0]), c2 = y_class(c, g0), c3 = split_class(g0.s[2]);
+            const bool split2 = c2 != kLenGeneric;
+            const int c13 = std::max(c1, c3), c123 = split2 ? std::max(c13, c2) : c13;
+            if (c->grad_mode > 0) {
+                add(KF_GRAD, off[KF_GRAD], cnt[KF_GRAD], 0, {KF_GRAD});
+                add(KF_DIV, off[KF_GRAD], cnt[KF_GRAD], 0, {KF_GRAD});
+            } else {
+                // gradient: the three directions are independent (one launch),
+                // but in general cells the axis-1 pass combines them
+                if (!split2) add(KG_Y, off[KD_Y], cnt[KD_Y], kLenGeneric, {KG_Y});
+                const int lo = split2 ? KD_Y : KD_X, n2 = split2 ? cnt[KD_Y] : 0;
+                if (!g0.general) {
+                    if (split2) add(KG_X, off[lo], n2 + cnt[KD_X] + cnt[KD_Z], c123, {KG_X, KG_Y, KG_Z});
+                    else add(KG_X, off[lo], cnt[KD_X] + cnt[KD_Z], c13, {KG_X, KG_Z});
+                } else {
+                    if (split2) add(KG_X, off[lo], n2 + cnt[KD_X], std::max(c2, c3), {KG_X, KG_Y});
+                    else add(KG_X, off[lo], cnt[KD_X], c3, {KG_X});
+                    add(KG_Z, off[KD_Z], cnt[KD_Z], c1, {KG_Z});
                 }
-                for (int grp = 0; grp < c->ngroups; ++grp) {
-                    vdwnl_ctx::Launch &L = ls[grp];
-                    L.kind = k;
-                    L.off = first[grp];
-                    L.cnt = count[grp];
-                    L.group = grp;
-                    if (L.cnt > 0) c->launches[k].push_back(L);
-                }
+                add(KD_X, off[KD_X], cnt[KD_X], c3, {KD_X});
+                add(KD_Y, off[KD_Y], cnt[KD_Y], c2, {KD_Y});
+                add(KD_Z, off[KD_Z], cnt[KD_Z], c1, {KD_Z});
             }
+            add(KX_THETA, off[KX_THETA], cnt[KX_THETA], c3, {KX_THETA});
+            add(KY_20F, off[KY_20F], cnt[KY_20F], c2, {KY_20F});
+            add(KZ_MAIN, off[KZ_MAIN], cnt[KZ_MAIN], c1, {KZ_MAIN});
+            add(KY_20I, off[KY_20F] - ng, cnt[KY_20F] + ng, c2, {KY_20I});
+            add(KX_ASSEMBLE, off[KX_THETA], cnt[KX_THETA], c3, {KX_THETA});
         }
     }
     // twiddles
@@ -1104,7 +1141,7 @@ static int lds_optin(vdwnl_ctx *c) {
     hipError_t e;
     for (int k = 0; k < KIND_COUNT; ++k)
         for (const auto &L : c->launches[k]) {
-            LaunchArgs a{nullptr, nullptr, 0, L.lds, nullptr, nullptr, nullptr, nullptr, nullptr, L.general, L.mfma, L.var, L.packed, L.threads};
+            LaunchArgs a{nullptr, nullptr, 0, L.lds, nullptr, nullptr, nullptr, nullptr, nullptr, L.general, L.mfma, L.packed, L.threads, L.len};
             if ((e = launch_kind(k, L.lc, c->precision, a)) != hipSuccess) return hipfail(c, e, "kernel LDS limit");
             // (and the stage probes that stand in for the pass)
             for (int pr : {PROBE_THETA_K, PROBE_U_K, PROBE_U}) {
@@ -1181,7 +1218,8 @@ static int upload_image(vdwnl_ctx *c, const Image &im, const DevPtrs &P, hipStre
 
 // The per-grid entries of the instance table for a buffer at base (the
 // density and potential pointers and the functional switch are kept).
-static void fill_insts(vdwnl_ctx *c, char *w, InstDev *out) {
+static void fill_insts(vdwnl_ctx *c, const DevPtrs &P, InstDev *out) {
+    char *w = P.base;
     const size_t ng = c->grids.size();
     for (size_t gi = 0; gi < ng; ++gi) {
         const Grid &g = c->grids[gi];
@@ -1194,6 +1232,7 @@ static void fill_insts(vdwnl_ctx *c, char *w, InstDev *out) {
         I.v = v_keep;
         I.semilocal = sl_keep;
         I.n1 = g.s[0]; I.n2 = g.s[1]; I.n3 = g.s[2]; I.n3h = g.s[2] / 2 + 1;
+        I.dn3h = div_magic(I.n3h);
         I.h1 = g.s[0] / 2 + 1; I.h2 = g.s[1] / 2 + 1;
         I.p1 = g.p1; I.p2 = g.p2; I.p3 = g.p3;
         I.inv_n = 1.0 / (double)g.npts();
@@ -1222,7 +1261,9 @@ static void fill_insts(vdwnl_ctx *c, char *w, InstDev *out) {
         I.part_ek = (double *)(w + g.off_ek); I.part_de = (double *)(w + g.off_de);
         I.part_sl = (double *)(w + g.off_sl);
         I.bad = (int *)(w + g.off_bad);
+        I.E = P.E + 4 * gi;
         I.n_ek = g.n_ek; I.n_de = g.n_de;
+        I.zthreads = zmain_threads(g, g.k3main, c->precision == 64 ? 16 : 8);
     }
 }
 
@@ -1285,13 +1326,13 @@ static int prepare_device(vdwnl_ctx *c) {
     if ((rc = upload_image(c, *im, c->dp, 0)) != VDWNL_OK) return rc;
     if ((e = hipStreamSynchronize(0)) != hipSuccess) return hipfail(c, e, "upload");
     std::memset(c->h_inst, 0, ng * sizeof(InstDev));
-    fill_insts(c, (char *)c->work, c->h_inst);
+    fill_insts(c, c->dp, c->h_inst);
     c->device_ready = true;
     return VDWNL_OK;
 }
 
 // Enqueue one evaluation on st: the instance table (device pointers of this
-// call's n and v), the passes of the gradient mode, the reduction and the copy of the
+// call's n and v), the passes of the gradient mode and the copy of the
 // energies to pinned host memory.  With timing on, events bracket each pass.
 // With chains (graph capture of a batch of several groups) each group's
 // passes go to a stream of its own, forked from st and joined back before
@@ -1306,7 +1347,7 @@ static int enqueue(vdwnl_ctx *c, const DevPtrs &P, const InstDev *hinst, double 
     const int *order;
     const int npass = pass_order(c->grad_mode, &order);
     auto launch = [&](const vdwnl_ctx::Launch &L, hipStream_t s) -> int {
-        LaunchArgs a{P.inst, P.tiles + L.off, L.cnt, L.lds, P.consts, P.tw, P.twd, s, P.cols, L.general, L.mfma, L.var, L.packed, L.threads};
+        LaunchArgs a{P.inst, P.tiles + L.off, L.cnt, L.lds, P.consts, P.tw, P.twd, s, P.cols, L.general, L.mfma, L.packed, L.threads, L.len};
         const hipError_t le = launch_kind(L.kind, L.lc, c->precision, a);
         return le == hipSuccess ? VDWNL_OK : hipfail(c, le, "kernel launch");
     };
@@ -1333,7 +1374,6 @@ static int enqueue(vdwnl_ctx *c, const DevPtrs &P, const InstDev *hinst, double 
             if (c->timing) (void)hipEventRecord(c->ev[i + 1], st);
         }
     }
-    if ((e = launch_reduce(P.inst, nb, P.E, st)) != hipSuccess) return hipfail(c, e, "reduce launch");
     if (c->timing) (void)hipEventRecord(c->ev[npass + 1], st);
     if ((e = hipMemcpyAsync(hE, P.E, nb * 4 * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess)
         return hipfail(c, e, "copy energies");
@@ -1472,7 +1512,7 @@ static int probe_stage(vdwnl_ctx *c, int stage, int target, void *dst, hipStream
     }
     auto args = [&](const vdwnl_ctx::Launch &L) {
         return LaunchArgs{c->dp.inst, c->dp.tiles + L.off, L.cnt, L.lds, c->dp.consts, c->dp.tw, c->dp.twd, st, c->dp.cols,
-                          L.general, L.mfma, L.var, L.packed, L.threads};
+                          L.general, L.mfma, L.packed, L.threads, L.len};
     };
     for (int i = 0; i < npass && order[i] != stop; ++i)
         for (const auto &L : c->launches[order[i]])
@@ -1608,7 +1648,7 @@ static int run_noalloc(vdwnl_ctx *c, const void *n_dev, void *v_dev, double *E_o
         }
     }
     InstDev *hi = c->na_inst.data();
-    fill_insts(c, slot.ptr, hi);
+    fill_insts(c, P, hi);
     hi[0].n = n_dev;
     hi[0].v = v_dev;
     hi[0].semilocal = c->functional == VDWNL_FUNCTIONAL_VDW_DF;
@@ -1913,7 +1953,7 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
         if (b <= ctx->lds_cap) cand.push_back(b);
     const bool timing0 = ctx->timing;
     ctx->img_valid = false;     // (the candidates' tiles differ from the image's)
-    for (auto &x : ctx->variant) x = 0;   // (the budgets are tuned with the first radix orders)
+    for (auto &x : ctx->variant) x = 0;
     // contraction units to try: the vector ALU, and the matrix cores where
     // some grid takes them (FP32, orthorhombic cell)
     std::vector<int> units = {VDWNL_CONTRACTION_VECTOR};
@@ -1971,51 +2011,6 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
     }
     ctx->contraction = best_unit;
     for (int gi = 0; gi < TG_COUNT; ++gi) ctx->pref[gi] = best[gi];
-    // budgets and radix orders together, with the chosen unit: every group at
-    // budget b and order v (each length class clamps v to its last variant)
-    // for v = 0 .. kMaxVariants - 1 and every candidate b (order 0 timed
-    // again, so that the pairs compared come from one stretch of runs), and
-    // per group the pair with the least time over the group's passes (a
-    // radix order changes the lanes per line, so the best tile width can
-    // move with it)
-    {
-        // tv[v][candidate][pass kind]
-        std::vector<std::vector<std::vector<double>>> tv(
-            kMaxVariants, std::vector<std::vector<double>>(cand.size(), std::vector<double>(KIND_COUNT, 0.0)));
-        for (int v = 0; v < kMaxVariants && rc == VDWNL_OK; ++v)
-            for (size_t ci = 0; ci < cand.size() && rc == VDWNL_OK; ++ci) {
-                for (auto &x : ctx->variant) x = v;
-                for (auto &p : ctx->pref) p = cand[ci];
-                for (auto &g : ctx->grids) size_tiles(ctx, g);
-                free_device(ctx);
-                ctx->timing = false;
-                rc = run(ctx, nb, n_ptrs, v_ptrs, E.data(), stream);
-                if (rc != VDWNL_OK) break;
-                vdwnl_set_timing(ctx, 1);
-                for (int r = 0; r < reps && rc == VDWNL_OK; ++r) rc = run(ctx, nb, n_ptrs, v_ptrs, E.data(), stream);
-                for (int k = 0; k < KIND_COUNT; ++k) tv[v][ci][k] = ctx->pass_ms[k];
-            }
-        for (int gi = 0; gi < TG_COUNT; ++gi) {
-            double bt = 1e300;
-            int bv = 0;
-            size_t bb = best[gi];
-            for (int v = 0; rc == VDWNL_OK && v < kMaxVariants; ++v)
-                for (size_t ci = 0; ci < cand.size(); ++ci) {
-                    // (every pass whose transforms take the group's order: the
-                    // axis-3 group's FP64 derivative passes too)
-                    double sum = 0.0;
-                    for (int k = 0; k < KIND_COUNT; ++k)
-                        if (k != KF_GRAD && k != KF_DIV && variant_group(k) == gi) sum += tv[v][ci][k];
-                    if (sum > 0.0 && sum < bt) {
-                        bt = sum;
-                        bv = v;
-                        bb = cand[ci];
-                    }
-                }
-            ctx->variant[gi] = bv;
-            ctx->pref[gi] = bb;
-        }
-    }
     for (auto &g : ctx->grids) size_tiles(ctx, g);
     free_device(ctx);
     refresh_image(ctx);

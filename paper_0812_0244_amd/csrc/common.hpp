@@ -15,12 +15,16 @@ constexpr size_t kFullRowCacheBytes = (size_t)256 << 20;   // a general-cell tab
 constexpr int kThreads = 256;                    // threads per workgroup, every kernel
 constexpr int kTileCap = 4096;                   // complex elements of one LDS FFT tile
 constexpr int kLdsCap = 65536;                   // bytes of LDS one workgroup may take
+constexpr size_t kReduceLds = 4 * 256 * sizeof(double);   // running sums of the energy reduction
 constexpr int kMaxStages = 16;
-constexpr int kYC = 16;                          // 16-byte chunks per row of an axis-2 tile of the 20 spectra
+// Most threads of a workgroup.  Five to seven waves do not spread evenly over
+// a CU's four SIMDs: the theta pass of 160 x 160 x 320 takes 317 us with 256
+// threads and 506 with 320, of four 128^3 grids 292 with 256 and 541 with 320
+// (the same tiles).
+constexpr int kMaxThreads = 256;
 constexpr int kMaxMc = 64;                       // largest m_c of Eq. (Sat)
 constexpr int kMaxFd = 4;                        // largest finite-difference half-width
 constexpr int kMaxN1 = 204;                      // (fused axis-1 pass; its lengths split into radices to 25)
-constexpr int kMaxN3 = 340;                      // 12 N3 complex doubles <= kLdsCap
 
 // One 1-D FFT length: radix sequence (each 2, 3, 4, 5 or 8) and the offset of
 // its twiddles W_n^k = exp(-2 pi i k / n), k < n, in the twiddle table.
@@ -30,6 +34,7 @@ struct FftPlan {
     int radix[kMaxStages];
     int tw;
     int r1, r2;              // the length as two radices (fft_split.hpp), 0 where it has no such split
+    uint32_t d1, d2, dn;     // div_magic of r1, r2 and n
 };
 
 // Per-grid state seen by the kernels.  Field layouts (C order):
@@ -46,6 +51,7 @@ struct FftPlan {
 //                   [nshell][kNQ (kNQ + 1) / 2] (packed upper triangle; some general-cell tables)
 struct InstDev {
     int n1, n2, n3, n3h, h1, h2;
+    uint32_t dn3h;           // div_magic of n3h
     FftPlan p1, p2, p3;
     double inv_n;            // 1 / (N1 N2 N3)
     double B[3][3];          // reciprocal vectors b_c (rows, Cartesian): G = sum_c m_c b_c
@@ -60,8 +66,10 @@ struct InstDev {
     double *part_ek;         // one partial per fused axis-1 tile
     double *part_de;         // one partial per theta tile
     double *part_sl;         // two per theta tile: E_x and E_c^LDA partials
+    double *E;               // the grid's energies: E_k, Delta E, E_x, E_c^LDA
     int *bad;                // set when a density value is negative, NaN or infinite
     int n_ek, n_de;
+    int zthreads;            // threads of the grid's fused axis-1 tiles
     int semilocal;           // add the semilocal terms of Eq. (Exc) (per call)
     const void *n;           // per call
     void *v;                 // per call
@@ -121,9 +129,9 @@ struct LaunchArgs {
     const int2 *cols;        // (k2, k3) columns of the fused axis-1 tiles
     int general;             // the launch's grids have non-orthogonal cells (packed shell rows)
     int mfma = 0;            // FP32 orthorhombic fused axis-1 pass: contraction on the matrix cores
-    int var = 0;             // radix order of the pass's transform length (0 .. its variants - 1)
     int packed = 0;          // (general cells) the launch's shell tables hold packed upper triangles
     int threads = kThreads;  // threads per workgroup
+    int len = 0;             // (axis-3 passes) the length, where it is one with a compile-time kernel
     void *dst = nullptr;     // (stage probes) the probe's output
     int target = 0;          // (stage probes) the grid whose tiles run
 };
@@ -138,13 +146,13 @@ enum ProbeLaunch { KP_THETA = KIND_COUNT + 1, KP_THETA_K, KP_U_K, KP_U };
 
 hipError_t launch_kind(int kind, int len_class, int precision, const LaunchArgs &a);
 hipError_t launch_probe(int probe, int len_class, int precision, const LaunchArgs &a, void *dst, int target);
-// family launchers (kernels_f32_x.hip ...): kind, length class, radix order
-hipError_t launch_x_f32(int kind, int lc, int var, const LaunchArgs &a);
-hipError_t launch_y_f32(int kind, int lc, int var, const LaunchArgs &a);
-hipError_t launch_z_f32(int kind, int lc, int var, const LaunchArgs &a);
-hipError_t launch_x_f64(int kind, int lc, int var, const LaunchArgs &a);
-hipError_t launch_y_f64(int kind, int lc, int var, const LaunchArgs &a);
-hipError_t launch_z_f64(int kind, int lc, int var, const LaunchArgs &a);
-hipError_t launch_reduce(const InstDev *insts, int ninst, double *E, hipStream_t stream);
+// family launchers (kernels_f32_x.hip ...) by split class: axis-3 passes (x),
+// axis-2 passes and the one-axis derivatives (y), the fused axis-1 pass (z)
+hipError_t launch_x_f32(int kind, int cls, const LaunchArgs &a);
+hipError_t launch_y_f32(int kind, int cls, const LaunchArgs &a);
+hipError_t launch_z_f32(int kind, int cls, const LaunchArgs &a);
+hipError_t launch_x_f64(int kind, int cls, const LaunchArgs &a);
+hipError_t launch_y_f64(int kind, int cls, const LaunchArgs &a);
+hipError_t launch_z_f64(int kind, int cls, const LaunchArgs &a);
 
 }  // namespace vdwnl

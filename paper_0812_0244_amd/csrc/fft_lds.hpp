@@ -159,7 +159,7 @@ __device__ __forceinline__ void load_twiddles(C2<T> *dst, const FftPlan &p, cons
     // is not waited for at a branch
     const int n = p.n;
     const C2<T> v0 = twall[p.tw + min((int)threadIdx.x, n - 1)];
-    for (int i = threadIdx.x + kThreads; i < n; i += kThreads) dst[i] = twall[p.tw + i];
+    for (int i = threadIdx.x + blockDim.x; i < n; i += blockDim.x) dst[i] = twall[p.tw + i];
     if ((int)threadIdx.x < n) dst[threadIdx.x] = v0;
 }
 

@@ -19,11 +19,11 @@ namespace vdwnl {
 
 // Radices of the split transforms.  A kernel is compiled for a largest radix
 // (its class) since the largest DFT sets the registers of all its lengths:
-// up to 10 (most lengths to 100), 16 (to 256) and 27 (to 405).
+// up to 10 (most lengths to 100), 16 (to 256), 20 (to 400) and 27 (to 405).
 constexpr int kSplitRadices[] = {1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27};
-constexpr int kSplitClassMax[] = {10, 16, 27};
-constexpr int kZClassMax[] = {10, 16, 25};        // (the fused axis-1 pass: lengths to 204)
-constexpr int kNumSplitClasses = 3;
+constexpr int kSplitClassMax[] = {10, 16, 20, 27};
+constexpr int kZClassMax[] = {10, 16, 20, 25};      // (the fused axis-1 pass: lengths to 204)
+constexpr int kNumSplitClasses = 4;
 constexpr int kSplitMaxLen = 405;
 
 // The most even split of n into two radices, r1 <= r2 (false: none).
@@ -45,6 +45,11 @@ inline int split_class(int n) {
     return kLenGeneric;
 }
 
+// log2 of the lanes along a tile (16-byte chunks of a row, or derivative
+// lines) in the passes with an item per thread: 16, or 8 where 16 R2 threads
+// would exceed a workgroup.
+constexpr int tile_lanes(int rmax) { return 16 * rmax <= kMaxThreads ? 4 : 3; }
+
 // f(integral_constant<R>) for the run-time radix r <= RMAX (uniform).
 template <int RMAX, typename F>
 __device__ __forceinline__ void with_radix(int r, F &&f) {
@@ -57,6 +62,17 @@ __device__ __forceinline__ void with_radix(int r, F &&f) {
     }
 #undef VDWNL_RADIX
 }
+
+// Division of items and positions by a run-time length: x / d as the high
+// half of x m, m = floor(2^32 / d) + 1, exact while x d < 2^32 (items of a tile
+// and positions in a row stay below 2^16, as do the divisors).  A run-time
+// integer division takes some twenty instructions, several times per thread.
+// m comes from the host with the plan (0 for d = 1).
+constexpr uint32_t div_magic(int d) { return d > 1 ? 0xffffffffu / (uint32_t)d + 1u : 0u; }
+struct FastDiv {
+    uint32_t m;
+    __device__ __forceinline__ int operator()(int x) const { return m ? (int)__umulhi((uint32_t)x, m) : x; }
+};
 
 // 16-byte chunks of complex values: two in FP32, one in FP64.
 template <typename T> struct Chunk;
@@ -81,6 +97,16 @@ __device__ __forceinline__ void split_twiddles(C2<T> *w, const C2<T> *tw, int j)
 #pragma unroll
     for (int k = 1; k < R; ++k) {
         w[k - 1] = gld(tw)[j * k];
+        if (S > 0) w[k - 1].y = -w[k - 1].y;
+    }
+}
+
+// The same from a copy of the table in LDS.
+template <typename T, int S, int R>
+__device__ __forceinline__ void lds_twiddles(C2<T> *w, const C2<T> *tw, int j) {
+#pragma unroll
+    for (int k = 1; k < R; ++k) {
+        w[k - 1] = tw[j * k];
         if (S > 0) w[k - 1].y = -w[k - 1].y;
     }
 }

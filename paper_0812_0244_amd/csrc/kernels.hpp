@@ -84,34 +84,18 @@ template <> __device__ __forceinline__ float dev_expm1(float x) {
 }
 template <> __device__ __forceinline__ double dev_expm1(double x) { return expm1(x); }
 
-// signed frequency index of position k on an axis of N points, 0 at Nyquist
-__device__ __forceinline__ int freq_nz(int k, int N) {
-    int m = (k <= N / 2) ? k : k - N;
-    if ((N & 1) == 0 && k == N / 2) m = 0;
-    return m;
-}
 __device__ __forceinline__ int freq_abs(int k, int N) { return k <= N - k ? k : N - k; }
 
-// Cartesian components of G = m1 b_1 + m2 b_2 + m3 b_3 (the frequencies with
-// Nyquist taken as zero); in an orthorhombic cell the off-diagonal b_c,x are
-// zero and each component is the single product m_c b_c,c exactly.
-template <typename T>
-__device__ __forceinline__ void cart_g(const InstDev &I, double m1, double m2, double m3, T &gx, T &gy, T &gz) {
-    gx = (T)(m1 * I.B[0][0] + m2 * I.B[1][0] + m3 * I.B[2][0]);
-    gy = (T)(m1 * I.B[0][1] + m2 * I.B[1][1] + m3 * I.B[2][1]);
-    gz = (T)(m1 * I.B[0][2] + m2 * I.B[1][2] + m3 * I.B[2][2]);
-}
-
-// Sum over the workgroup in a fixed order; result valid in thread 0.
+// Sum over the workgroup in a fixed order (at most eight waves); result valid
+// in thread 0.
 __device__ __forceinline__ double block_sum(double v) {
-    __shared__ double red[kThreads / 64];
+    __shared__ double red[8];
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) red[wave] = v;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = 0.0;
     if (threadIdx.x == 0)
-        for (int w = 0; w < kThreads / 64; ++w) s += red[w];
+        for (int w = 0; w < ((int)blockDim.x + 63) / 64; ++w) s += red[w];
     __syncthreads();
     return s;
 }
@@ -258,37 +242,121 @@ struct SplineW {
 };
 
 // q mesh, spline second derivatives and 1/m into LDS (in T); all loads are
-// issued before any store (indices clamped, the stores guarded)
+// issued before any store (indices clamped, the stores guarded).  At least
+// 128 threads.
 template <typename T>
 __device__ __forceinline__ void load_consts(const Consts *cst, T *qm, T *Mm, T *invm) {
-    static_assert(kNQ * kNQ <= 2 * kThreads && kNQ <= kThreads && kMaxMc < kThreads, "one or two steps each");
-    const int i = threadIdx.x, i2 = threadIdx.x + kThreads;
+    static_assert(kNQ * kNQ <= 4 * 128 && kNQ <= 128 && kMaxMc < 128, "four steps, one and one");
+    const int i = threadIdx.x, nt = blockDim.x;
     const gptr<const double> q = gld(cst->q), M = gld(cst->M), im = gld(cst->invm);
-    const double a = q[min(i, kNQ - 1)], b = M[min(i, kNQ * kNQ - 1)], b2 = M[min(i2, kNQ * kNQ - 1)];
-    const double c = im[min(i, kMaxMc)];
+    const double a = q[min(i, kNQ - 1)], c = im[min(i, kMaxMc)];
+    double m[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m[u] = M[min(i + u * nt, kNQ * kNQ - 1)];
     if (i < kNQ) qm[i] = (T)a;
-    if (i < kNQ * kNQ) Mm[i] = (T)b;
-    if (i2 < kNQ * kNQ) Mm[i2] = (T)b2;
     if (i <= kMaxMc) invm[i] = (T)c;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (i + u * nt < kNQ * kNQ) Mm[i + u * nt] = (T)m[u];
 }
 
 // ---------------------------------------------------------------- axis-3 passes
 
+// Axis-3 tiles: B whole rows, the 20 fields in pairs (theta_2m + i theta_2m+1,
+// one complex line each), as split transforms in LDS.  Element n of a row
+// (later slot (r, j), n = j + R2 r, and frequency slot (k1, k2)) holds its ten
+// pair values contiguously: a point's thread moves them 16 bytes at a time, a
+// transform item is one pair line, and ten lanes run along the pairs.  Each
+// R2 elements are followed by a padding that keeps the lanes of neighbouring
+// items on different banks.
+// Compile-time radices (CR1 CR2 = the length; 0: run-time ones) turn the
+// positions and strides of the common lengths into constants.
+template <typename T, int CR1, int CR2>
+struct XTile {
+    static constexpr int kP = kNQ / 2;                        // pair lines per row
+    static constexpr int eb = kP * (int)sizeof(C2<T>);        // bytes per element
+    const FftPlan &p;
+    __device__ __forceinline__ explicit XTile(const FftPlan &p_) : p(p_) {}
+    __device__ __forceinline__ int R1() const { if constexpr (CR1 > 0) return CR1; else return p.r1; }
+    __device__ __forceinline__ int R2() const { if constexpr (CR1 > 0) return CR2; else return p.r2; }
+    __device__ __forceinline__ int len() const { if constexpr (CR1 > 0) return CR1 * CR2; else return p.n; }
+    __device__ __forceinline__ int by1(int x) const { if constexpr (CR1 > 0) return x / CR1; else return FastDiv{p.d1}(x); }
+    __device__ __forceinline__ int by2(int x) const { if constexpr (CR1 > 0) return x / CR2; else return FastDiv{p.d2}(x); }
+    __device__ __forceinline__ int byn(int x) const { if constexpr (CR1 > 0) return x / (CR1 * CR2); else return FastDiv{p.dn}(x); }
+    __device__ __forceinline__ int gs() const { return __mul24(R2(), eb) + (__mul24(1 - R2(), eb) & 255); }   // bytes per R2 elements
+    __device__ __forceinline__ int rs() const { return __mul24(R1(), gs()); }                            // and per row
+    __device__ __forceinline__ int elem(int n) const { const int r = by2(n); return __mul24(r, gs()) + __mul24(n - __mul24(r, R2()), eb); }
+    __device__ __forceinline__ int freq(int k) const { const int k2 = by1(k); return __mul24(k - __mul24(k2, R1()), gs()) + __mul24(k2, eb); }
+};
+
+// Both steps of the transform of a tile's B rows, in place: forward (S = -1)
+// elements -> frequency slots, inverse (S = 1) back; tw: the length's table in
+// LDS.  Synchronised by the caller before; synchronises between the steps and
+// after.
+template <typename T, int S, int RMAX, int CR1, int CR2>
+__device__ __forceinline__ void xtile_fft(unsigned char *buf, const XTile<T, CR1, CR2> &X, int B, const C2<T> *tw) {
+    constexpr int P = XTile<T, CR1, CR2>::kP;
+    const int nt = blockDim.x;
+    auto radix = [&](auto Cc, int r, auto &&f) {
+        if constexpr (decltype(Cc)::value > 0) f(Cc);
+        else with_radix<RMAX>(r, f);
+    };
+    auto one = [&]() {      // over r (or k1) at residue j
+        for (int it = threadIdx.x; it < B * X.R2() * P; it += nt) {
+            const int q = it / P, m = it - q * P, rb = X.by2(q), j = q - __mul24(rb, X.R2());
+            unsigned char *lb = buf + __mul24(rb, X.rs()) + j * X.eb + m * (int)sizeof(C2<T>);
+            radix(std::integral_constant<int, CR1>{}, X.R1(), [&](auto Rc) {
+                constexpr int R = decltype(Rc)::value;
+                C2<T> x[R], w[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[r] = *reinterpret_cast<const C2<T> *>(lb + r * X.gs());
+                Dft<T, R, S>::run(x);
+                if (S < 0) lds_twiddles<T, S, R>(w, tw, j);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    *reinterpret_cast<C2<T> *>(lb + r * X.gs()) = (S > 0 || r == 0) ? x[r] : cmul(x[r], w[r - 1]);
+            });
+        }
+        __syncthreads();
+    };
+    auto two = [&]() {      // over j (or k2) at k1
+        for (int it = threadIdx.x; it < B * X.R1() * P; it += nt) {
+            const int q = it / P, m = it - q * P, rb = X.by1(q), k1 = q - __mul24(rb, X.R1());
+            unsigned char *lb = buf + __mul24(rb, X.rs()) + __mul24(k1, X.gs()) + m * (int)sizeof(C2<T>);
+            radix(std::integral_constant<int, CR2>{}, X.R2(), [&](auto Rc) {
+                constexpr int R = decltype(Rc)::value;
+                C2<T> x[R], w[R];
+#pragma unroll
+                for (int j = 0; j < R; ++j) x[j] = *reinterpret_cast<const C2<T> *>(lb + j * X.eb);
+                Dft<T, R, S>::run(x);
+                if (S > 0) lds_twiddles<T, S, R>(w, tw, k1);
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+                    *reinterpret_cast<C2<T> *>(lb + j * X.eb) = (S < 0 || j == 0) ? x[j] : cmul(x[j], w[j - 1]);
+            });
+        }
+        __syncthreads();
+    };
+    if (S < 0) { one(); two(); }
+    else { two(); one(); }
+}
+
 // theta_a = n p_a(q0) from n and the stored grad n, Delta E partials, R2C of
 // the 20 theta rows.  tile: a = first row, b = rows, slot = partial.
-template <typename T, int LC, int V>
-__global__ void __launch_bounds__(kThreads) k_x_theta(const InstDev *insts, const Tile *tiles,
-                                                      const Consts *cst, const void *twv) {
+template <typename T, int RMAX, int CR1, int CR2>
+__global__ void __launch_bounds__(kMaxThreads, sizeof(T) == 8 ? 2 : RMAX <= 16 ? 5 : 4) k_x_theta(const InstDev *insts, const Tile *tiles, const Consts *cst,
+                                                        const void *twv) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Tile t = tiles[blockIdx.x];
     const InstDev &I = insts[t.inst];
-    const int N3 = axis_len<LC>(I.n3), N3h = N3 / 2 + 1, row0 = t.a, B = t.b, ls = N3 + 1;
+    const XTile<T, CR1, CR2> X(I.p3);
+    const int N3 = X.len(), N3h = N3 / 2 + 1, row0 = t.a, B = t.b, nt = blockDim.x;
     const size_t N = (size_t)I.n1 * I.n2 * I.n3;
-    C2<T> *r2 = reinterpret_cast<C2<T> *>(smem);              // 10 lines per row: theta pairs
-    C2<T> *tw = r2 + kNQ / 2 * B * ls;                       // twiddles in T
+    C2<T> *tw = reinterpret_cast<C2<T> *>(smem + B * X.rs());
     T *qm = reinterpret_cast<T *>(tw + N3);
     T *Mm = qm + kNQ;
     T *invm = Mm + kNQ * kNQ;
+    int *fo = reinterpret_cast<int *>(invm + kMaxMc + 1);     // (run-time radices) slot of every frequency
     // density and grad n of this thread's first point, fetched first (used
     // after the constants arrive); unconditional loads, clamped to the tile: a
     // load under a branch would be waited for where the branch joins
@@ -300,19 +368,21 @@ __global__ void __launch_bounds__(kThreads) k_x_theta(const InstDev *insts, cons
     const T n_first = nin[i_first], gx_f = gin[i_first], gy_f = gin[N + i_first], gz_f = gin[2 * N + i_first];
     load_consts<T>(cst, qm, Mm, invm);
     load_twiddles<T>(tw, I.p3, reinterpret_cast<const C2<T> *>(twv));
+    if (CR1 == 0)
+        for (int k = threadIdx.x; k < N3; k += nt) fo[k] = X.freq(k);
     __syncthreads();
 
     const double c_qc = cst->qc, c_iqc = cst->iqc, c_cs = cst->cs, c_nmin = cst->nmin;
     const int c_mc = cst->mc;
     const bool semilocal = I.semilocal != 0;
     double de = 0.0, dex = 0.0, dec = 0.0;
-    for (int idx = threadIdx.x; idx < npt; idx += kThreads) {
-        const int rb = idx / N3, k = idx - rb * N3;
+    for (int idx = threadIdx.x; idx < npt; idx += nt) {
+        const int rb = X.byn(idx), k = idx - __mul24(rb, N3);
         const bool first = idx == (int)threadIdx.x;
         const T nv = first ? n_first : nin[idx];
         const C2<T> g01 = mk<T>(first ? gx_f : gin[idx], first ? gy_f : gin[N + idx]);
         const C2<T> g2 = mk<T>(first ? gz_f : gin[2 * N + idx], (T)0);
-        T *th = reinterpret_cast<T *>(r2 + (size_t)(kNQ / 2 * rb) * ls);   // pair line m at th + 2 m ls
+        C2<T> *thc = reinterpret_cast<C2<T> *>(smem + __mul24(rb, X.rs()) + X.elem(k));   // the point's ten pairs
         // a density the method is not defined for (negative, NaN, infinite):
         // flag the grid (its energies come out NaN, the call reports it)
         if (!(nv >= (T)0 && nv <= finite_max<T>())) gst(I.bad)[0] = 1;
@@ -330,12 +400,17 @@ __global__ void __launch_bounds__(kThreads) k_x_theta(const InstDev *insts, cons
             sw.locate(lq.q0, qm, kNQ);
             const T *Mj = Mm + sw.j * kNQ;
             const T nC0 = nv * sw.C0, nC1 = nv * sw.C1;
-            // pair m = (theta_2m, theta_2m+1) as one 8- or 16-byte store: lanes
-            // (consecutive k) then touch consecutive LDS words
-            C2<T> *thc = reinterpret_cast<C2<T> *>(th) + k;   // pair line m at thc[m ls]
+            // (16 bytes a store: lanes 80 or 160 bytes apart on different banks)
 #pragma unroll
-            for (int m = 0; m < kNQ / 2; ++m)
-                thc[m * ls] = mk<T>(nC0 * Mj[2 * m] + nC1 * Mj[kNQ + 2 * m], nC0 * Mj[2 * m + 1] + nC1 * Mj[kNQ + 2 * m + 1]);
+            for (int h = 0; h < kNQ / 2 / Chunk<T>::N; ++h) {
+                C2<T> a[Chunk<T>::N];
+#pragma unroll
+                for (int q = 0; q < Chunk<T>::N; ++q) {
+                    const int m = Chunk<T>::N * h + q;
+                    a[q] = mk<T>(nC0 * Mj[2 * m] + nC1 * Mj[kNQ + 2 * m], nC0 * Mj[2 * m + 1] + nC1 * Mj[kNQ + 2 * m + 1]);
+                }
+                reinterpret_cast<typename Chunk<T>::V *>(thc)[h] = Chunk<T>::join(a);
+            }
             // the interpolating parts A0 d_aj + A1 d_a,j+1 touch components j and
             // j + 1: rewrite the pair (j even) or the two pairs (j odd) that hold
             // them (same thread, so after the loop's stores)
@@ -343,28 +418,29 @@ __global__ void __launch_bounds__(kThreads) k_x_theta(const InstDev *insts, cons
             const bool odd = (j0 & 1) != 0;
             const T nA0 = nv * sw.A0, nA1 = nv * sw.A1;
             const T *M0 = Mj + 2 * m0, *M1 = Mj + kNQ + 2 * m0;
-            thc[m0 * ls] = mk<T>(nC0 * M0[0] + nC1 * M1[0] + (odd ? (T)0 : nA0), nC0 * M0[1] + nC1 * M1[1] + (odd ? nA0 : nA1));
-            if (odd) thc[(m0 + 1) * ls] = mk<T>(nC0 * M0[2] + nC1 * M1[2] + nA1, nC0 * M0[3] + nC1 * M1[3]);
+            thc[m0] = mk<T>(nC0 * M0[0] + nC1 * M1[0] + (odd ? (T)0 : nA0), nC0 * M0[1] + nC1 * M1[1] + (odd ? nA0 : nA1));
+            if (odd) thc[m0 + 1] = mk<T>(nC0 * M0[2] + nC1 * M1[2] + nA1, nC0 * M0[3] + nC1 * M1[3]);
             const T iq = rcp<T>(lq.q0);
             de += (double)((T)c_cs * nv * nv * iq * iq * iq);
         } else {
-            C2<T> *thc = reinterpret_cast<C2<T> *>(th) + k;
 #pragma unroll
-            for (int m = 0; m < kNQ / 2; ++m) thc[m * ls] = mk<T>((T)0, (T)0);
+            for (int m = 0; m < kNQ / 2; ++m) thc[m] = mk<T>((T)0, (T)0);
         }
     }
     __syncthreads();
-    fft_lc<T, -1, LC, V>(r2, I.p3, kNQ / 2 * B, 1, ls, tw);
+    xtile_fft<T, -1, RMAX, CR1, CR2>(smem, X, B, tw);
 
     // pair line m of row rb holds theta_{2m} + i theta_{2m+1}: its values at
     // k and N3 - k give both spectra at k, written together (item idx =
     // (rb N3h + k) 10 + m lands at spectrum element 2 idx)
     C2<T> *out = reinterpret_cast<C2<T> *>(I.spec) + (size_t)row0 * N3h * kNQ;
-    Cursor3 cur(threadIdx.x, kNQ / 2, N3h);
-    for (int idx = threadIdx.x; idx < B * N3h * (kNQ / 2); idx += kThreads, cur.step()) {
-        const int m = cur.m, k = cur.k, rb = cur.r;
-        const C2<T> *Z = r2 + (kNQ / 2 * rb + m) * ls;
-        const C2<T> z = Z[k], zc = cconj(Z[k == 0 ? 0 : N3 - k]);
+    auto by3h = [&](int x) { if constexpr (CR1 > 0) return x / (CR1 * CR2 / 2 + 1); else return FastDiv{I.dn3h}(x); };
+    for (int idx = threadIdx.x; idx < B * N3h * (kNQ / 2); idx += nt) {
+        const int q = idx / (kNQ / 2), m = idx - q * (kNQ / 2), rb = by3h(q), k = q - __mul24(rb, N3h);
+        const unsigned char *Z = smem + __mul24(rb, X.rs()) + m * (int)sizeof(C2<T>);
+        const int kc = k == 0 ? 0 : N3 - k;
+        const C2<T> z = *reinterpret_cast<const C2<T> *>(Z + (CR1 > 0 ? X.freq(k) : fo[k]));
+        const C2<T> zc = cconj(*reinterpret_cast<const C2<T> *>(Z + (CR1 > 0 ? X.freq(kc) : fo[kc])));
         const T ex = (z.x + zc.x) * (T)0.5, ey = (z.y + zc.y) * (T)0.5;
         const T ox = (z.y - zc.y) * (T)0.5, oy = -(z.x - zc.x) * (T)0.5;
         C2<T> *o = out + 2 * (size_t)idx;
@@ -385,39 +461,41 @@ __global__ void __launch_bounds__(kThreads) k_x_theta(const InstDev *insts, cons
 }
 
 // The u spectra of B rows (axis 3 half spectra, [B][N3h][kNQ] complex at sp)
-// into LDS pair lines ready for the inverse axis-3 FFT: u_{2m} + i u_{2m+1}
-// on pair line m of row rb (at r2 + (10 rb + m) ls), from the spectra at k
-// (< N3/2 + 1) both the value at k and, by Hermitian symmetry, at N3 - k.
-// Item idx = (rb N3h + k) 10 + m reads spectrum elements 2 idx, 2 idx + 1;
-// about five steps per thread for every length class: batches of six.
-template <typename T>
-__device__ __forceinline__ void u_lines_in(C2<T> *r2, int ls, const C2<T> *sp, int B, int N3, int N3h) {
-    constexpr int U = 6;
-    const int total = B * N3h * (kNQ / 2);
-    Cursor3 cur(threadIdx.x, kNQ / 2, N3h);
+// into the frequency slots, ready for the inverse axis-3 FFT: u_{2m} + i u_{2m+1}
+// of row rb, from the spectra at k (< N3/2 + 1) both the value at k and, by
+// Hermitian symmetry, at N3 - k.  Item idx = (rb N3h + k) 10 + m reads spectrum
+// elements 2 idx, 2 idx + 1; about five steps per thread: batches of six (four in FP64).
+template <typename T, int CR1, int CR2>
+__device__ __forceinline__ void u_lines_in(unsigned char *buf, const XTile<T, CR1, CR2> &X, const C2<T> *sp, int B,
+                                           uint32_t dn3h) {
+    constexpr int U = sizeof(T) == 4 ? 6 : 4, P = XTile<T, CR1, CR2>::kP;
+    const int N3 = X.len(), N3h = N3 / 2 + 1;
+    auto by3h = [&](int x) { if constexpr (CR1 > 0) return x / (CR1 * CR2 / 2 + 1); else return FastDiv{dn3h}(x); };
+    const int total = B * N3h * P, nt = blockDim.x;
     const gptr<const C2<T>> g = gld(sp);
-    for (int base = threadIdx.x; base < total; base += U * kThreads) {
-        C2<T> ya[U], yb[U];
-        int lo[U], kk[U];
+    for (int base = threadIdx.x; base < total; base += U * nt) {
+        T ax[U], ay[U], bx[U], by[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int idx = base + u * kThreads;
-            const bool on = idx < total;
-            const size_t e = on ? 2 * (size_t)idx : 0;   // (unconditional loads)
-            ya[u] = g[e];
-            yb[u] = g[e + 1];
-            lo[u] = on ? (kNQ / 2 * cur.r + cur.m) * ls : -1;
-            kk[u] = cur.k;
-            cur.step();
+            const int idx = base + u * nt;
+            const size_t e = idx < total ? 2 * (size_t)idx : 0;   // (unconditional loads)
+            if constexpr (sizeof(T) == 4) {
+                const float4 v = *(gptr<const float4>)(g + e);
+                ax[u] = v.x; ay[u] = v.y; bx[u] = v.z; by[u] = v.w;
+            } else {
+                const C2<T> a = g[e], b = g[e + 1];
+                ax[u] = a.x; ay[u] = a.y; bx[u] = b.x; by[u] = b.y;
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (lo[u] < 0) continue;
-            C2<T> *line = r2 + lo[u];
-            const int k = kk[u];
-            const C2<T> a = ya[u], b = yb[u];
-            line[k] = mk<T>(a.x - b.y, a.y + b.x);
-            if (k != 0 && 2 * k != N3) line[N3 - k] = mk<T>(a.x + b.y, -a.y + b.x);   // conj(a) + i conj(b)
+            const int idx = base + u * nt;
+            if (idx >= total) continue;
+            const int q = idx / P, m = idx - q * P, rb = by3h(q), k = q - __mul24(rb, N3h);
+            unsigned char *Z = buf + __mul24(rb, X.rs()) + m * (int)sizeof(C2<T>);
+            *reinterpret_cast<C2<T> *>(Z + X.freq(k)) = mk<T>(ax[u] - by[u], ay[u] + bx[u]);
+            // conj(a) + i conj(b)
+            if (k != 0 && 2 * k != N3) *reinterpret_cast<C2<T> *>(Z + X.freq(N3 - k)) = mk<T>(ax[u] + by[u], -ay[u] + bx[u]);
         }
     }
 }
@@ -426,19 +504,20 @@ __device__ __forceinline__ void u_lines_in(C2<T> *r2, int ls, const C2<T> *sp, i
 // w = g grad n with g = sum_a u_a 2 n p'_a Q dq/dsigma + de/dsigma-part,
 // stored in place of grad n as its lattice components q_c (the divergence
 // passes take them).  tile: a = first row, b = rows.
-template <typename T, int LC, int V>
-__global__ void __launch_bounds__(kThreads) k_x_assemble(const InstDev *insts, const Tile *tiles,
-                                                         const Consts *cst, const void *twv) {
+template <typename T, int RMAX, int CR1, int CR2>
+__global__ void __launch_bounds__(kMaxThreads, sizeof(T) == 8 ? (RMAX <= 16 || CR1 > 0 ? 3 : 2) : RMAX <= 16 ? 5 : 4) k_x_assemble(const InstDev *insts, const Tile *tiles, const Consts *cst,
+                                                           const void *twv) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Tile t = tiles[blockIdx.x];
     const InstDev &I = insts[t.inst];
-    const int N3 = axis_len<LC>(I.n3), N3h = N3 / 2 + 1, row0 = t.a, B = t.b, ls = N3 + 1;
+    const XTile<T, CR1, CR2> X(I.p3);
+    const int N3 = X.len(), N3h = N3 / 2 + 1, row0 = t.a, B = t.b, nt = blockDim.x;
     const size_t N = (size_t)I.n1 * I.n2 * I.n3;
-    C2<T> *r2 = reinterpret_cast<C2<T> *>(smem);              // 10 lines per row: u pairs
-    C2<T> *tw = r2 + kNQ / 2 * B * ls;                       // twiddles in T
+    C2<T> *tw = reinterpret_cast<C2<T> *>(smem + B * X.rs());
     T *qm = reinterpret_cast<T *>(tw + N3);
     T *Mm = qm + kNQ;
     T *invm = Mm + kNQ * kNQ;
+    load_twiddles<T>(tw, I.p3, reinterpret_cast<const C2<T> *>(twv));
     // n and grad n of this thread's first point, fetched first (used after the FFT)
     const int npt = B * N3;
     const size_t p0 = (size_t)row0 * N3;
@@ -448,18 +527,17 @@ __global__ void __launch_bounds__(kThreads) k_x_assemble(const InstDev *insts, c
     // be waited for where the branch joins)
     const int i_first = min((int)threadIdx.x, npt - 1);
     const T n_f = nin[i_first], gx_f = grad[i_first], gy_f = grad[N + i_first], gz_f = grad[2 * N + i_first];
-    u_lines_in<T>(r2, ls, reinterpret_cast<const C2<T> *>(I.spec) + (size_t)row0 * N3h * kNQ, B, N3, N3h);
+    u_lines_in(smem, X, reinterpret_cast<const C2<T> *>(I.spec) + (size_t)row0 * N3h * kNQ, B, I.dn3h);
     load_consts<T>(cst, qm, Mm, invm);
-    load_twiddles<T>(tw, I.p3, reinterpret_cast<const C2<T> *>(twv));
     __syncthreads();
-    fft_lc<T, 1, LC, V>(r2, I.p3, kNQ / 2 * B, 1, ls, tw);
+    xtile_fft<T, 1, RMAX, CR1, CR2>(smem, X, B, tw);
 
     const double c_qc = cst->qc, c_iqc = cst->iqc, c_cs = cst->cs, c_nmin = cst->nmin;
     const int c_mc = cst->mc;
     const bool semilocal = I.semilocal != 0;
     const gptr<T> vloc = gst(reinterpret_cast<T *>(I.vloc) + p0);
-    for (int idx = threadIdx.x; idx < npt; idx += kThreads) {
-        const int rb = idx / N3, k = idx - rb * N3;
+    for (int idx = threadIdx.x; idx < npt; idx += nt) {
+        const int rb = X.byn(idx), k = idx - __mul24(rb, N3);
         const bool first = idx == (int)threadIdx.x;
         const T nv = first ? n_f : nin[idx];
         const T gx = first ? gx_f : grad[idx], gy = first ? gy_f : grad[N + idx], gz = first ? gz_f : grad[2 * N + idx];
@@ -470,22 +548,25 @@ __global__ void __launch_bounds__(kThreads) k_x_assemble(const InstDev *insts, c
             lq.eval(nv, sigma, c_qc, c_iqc, c_mc, invm);
             SplineW<T> sw;
             sw.locate(lq.q0, qm, kNQ);
-            const T *u = reinterpret_cast<const T *>(r2 + (size_t)(kNQ / 2 * rb) * ls);
             const T cn = nv * lq.Q * lq.dqdn;
             // sum_a u_a p_a and sum_a u_a p_a' through S0 = sum_a u_a M[j][a], S1 = sum_a u_a M[j+1][a]
             const T *Mj = Mm + sw.j * kNQ;
             T S0 = (T)0, S1 = (T)0;
-            // pair m = (u_2m, u_2m+1) as one 8- or 16-byte load (lanes on
-            // consecutive k read consecutive LDS words)
-            const C2<T> *uc = reinterpret_cast<const C2<T> *>(u) + k;
+            const C2<T> *uc = reinterpret_cast<const C2<T> *>(smem + __mul24(rb, X.rs()) + X.elem(k));   // the point's ten pairs
+            const T *u = reinterpret_cast<const T *>(uc);
 #pragma unroll
-            for (int m = 0; m < kNQ / 2; ++m) {
-                const C2<T> up = uc[m * ls];
-                S0 += up.x * Mj[2 * m] + up.y * Mj[2 * m + 1];
-                S1 += up.x * Mj[kNQ + 2 * m] + up.y * Mj[kNQ + 2 * m + 1];
+            for (int h = 0; h < kNQ / 2 / Chunk<T>::N; ++h) {
+                C2<T> up[Chunk<T>::N];
+                Chunk<T>::split(reinterpret_cast<const typename Chunk<T>::V *>(uc)[h], up);
+#pragma unroll
+                for (int q = 0; q < Chunk<T>::N; ++q) {
+                    const int m = Chunk<T>::N * h + q;
+                    S0 += up[q].x * Mj[2 * m] + up[q].y * Mj[2 * m + 1];
+                    S1 += up[q].x * Mj[kNQ + 2 * m] + up[q].y * Mj[kNQ + 2 * m + 1];
+                }
             }
             const int j0 = sw.j, j1 = sw.j + 1;
-            const T uj = u[2 * ((j0 >> 1) * ls + k) + (j0 & 1)], uj1 = u[2 * ((j1 >> 1) * ls + k) + (j1 & 1)];
+            const T uj = u[j0], uj1 = u[j1];
             const T su = sw.A0 * uj + sw.A1 * uj1 + sw.C0 * S0 + sw.C1 * S1;
             const T sdu = sw.B0 * uj + sw.B1 * uj1 + sw.D0 * S0 + sw.D1 * S1;
             // dtheta_a/dn = p_a + n p'_a Q dq/dn ; dtheta_a/dgrad n = 2 n p'_a Q dq/dsigma grad n
@@ -648,6 +729,183 @@ __global__ void __launch_bounds__(kThreads) k_fd_div(const InstDev *insts, const
 // MODE 0 (gradient, FP64 lines): n -> d_c n; MODE 1 (divergence, lines in
 // the working precision): q_c -> the potential, v = v_loc - sum_c d_c q_c.
 
+// The lines of a tile as split transforms (fft_split.hpp): step two of the
+// forward transform, the factors i kappa_m and step two of the inverse stay in
+// the registers of one item, so a line crosses LDS twice.  One kernel takes
+// every axis (run-time strides), so the three independent gradient passes of
+// an orthorhombic grid are one launch.  Bound by the latency of its few
+// dependent steps on small grids, by memory on large ones (the three gradient
+// directions together 41 -> 13 us at 96^3 and 83 -> 18 at 90 x 100 x 108 in
+// FP32, 198 -> 78 at 160 x 160 x 320; the three divergence passes 43 -> 30,
+// 76 -> 33 and 143 -> 87).
+// tile: slot = axis (3, 2, 1); lanes = tile_lanes of the axis's R2.
+//   axis 3: a = first row (i1 N2 + i2), b = rows (even, <= 2 << lanes; rows 2p, 2p+1
+//     form line p).  MODE 0: grad[2] = W[2][2] d_3 n (orthorhombic) or d_3 n
+//     (general cells: the axis-1 pass combines); the grid's first tile, it
+//     also clears the bad-density flag.  MODE 1: v = v_loc - d_3 q_3 (q_3 in
+//     grad[2]).
+//   axes 2, 1 (lines along i2 at element stride N3, along i1 at N2 N3): a =
+//     the other outer index (i1, or i2), b = first i3, c = number of
+//     consecutive i3 (<= 2 << lanes; pairs form one line, an odd last one stands
+//     alone).  MODE 0, axis 2: grad[1] = W[1][1] d_2 n (orthorhombic) or d_2 n
+//     (general).  MODE 0, axis 1: grad[0] = W[0][0] d_1 n (orthorhombic);
+//     general cells, where it runs after the others: grad n = sum_c W[c] d_c n
+//     from d_1 n and the stored d_2 n, d_3 n, all three Cartesian components
+//     written.  MODE 1: v -= d_c q_c (q_c in grad[axis - 1]).
+template <typename T, typename C, int RMAX, int MODE>
+__global__ void __launch_bounds__(kMaxThreads, 2) k_deriv(const InstDev *insts, const Tile *tiles, const void *twv) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    C2<C> *buf = reinterpret_cast<C2<C> *>(smem);
+    const Tile t = tiles[blockIdx.x];
+    const InstDev &I = insts[t.inst];
+    const int axis = t.slot, ax = axis - 1;
+    const FftPlan &pl = axis == 3 ? I.p3 : axis == 2 ? I.p2 : I.p1;
+    const int L = pl.n, R1 = pl.r1, R2 = pl.r2, N3 = I.n3, lanes = tile_lanes(R2);
+    const size_t N = (size_t)I.n1 * I.n2 * N3;
+    const bool rows = axis == 3;
+    if (MODE == 0 && rows && t.a == 0 && threadIdx.x == 0) gst(I.bad)[0] = 0;
+    // element e of line l (its real part; the imaginary part pst further on)
+    // at base + l lst + e est; LDS slot (k1, j) of line l at l ls + k1 ks + j js
+    const int W = rows ? t.b : t.c, nl = (W + 1) / 2;
+    const int est = rows ? 1 : axis == 2 ? N3 : I.n2 * N3;         // (32-bit offsets: 3 N < 2^31)
+    const int lst = rows ? 2 * N3 : 2, pst = rows ? N3 : 1;
+    const size_t base = rows ? (size_t)t.a * N3 : (axis == 2 ? (size_t)t.a * I.n2 * N3 : (size_t)t.a * N3) + t.b;
+    const int js = rows ? 1 : 1 << lanes, ks = rows ? R2 | 1 : R2 << lanes, ls = rows ? R1 * ks : 1;
+    const C2<C> *tw = reinterpret_cast<const C2<C> *>(twv) + pl.tw;
+    // items: lanes run along the contiguous direction (residues of a row, or
+    // lines of a column tile)
+    const FastDiv by1{pl.d1}, by2{pl.d2};
+    const int q1 = rows ? by2(threadIdx.x) : (int)threadIdx.x & ((1 << lanes) - 1);
+    const int p1 = rows ? (int)threadIdx.x - q1 * R2 : (int)threadIdx.x >> lanes;
+    const int q2 = rows ? by1(threadIdx.x) : q1, p2 = rows ? (int)threadIdx.x - q2 * R1 : p1;
+    const bool on1 = q1 < nl && p1 < R2, on2 = q2 < nl && p2 < R1;
+    const int gofs = q1 * lst + p1 * est, po = 2 * q1 + 1 < W ? pst : 0;
+    typedef T pair_t __attribute__((ext_vector_type(2)));
+    // pairs as one access where the row length and the pointer allow it
+    auto pairable = [&](const void *ptr) { return !rows && ((N3 | W) & 1) == 0 && (reinterpret_cast<uintptr_t>(ptr) & (2 * sizeof(T) - 1)) == 0; };
+    const T *src = MODE == 0 ? reinterpret_cast<const T *>(I.n) + base : reinterpret_cast<const T *>(I.grad) + ax * N + base;
+    const bool vec = pairable(src);
+    if (on1)
+        with_radix<RMAX>(R1, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<C> w[R], x[R];
+            T re[R], im[R];
+            const gptr<const T> f = gld(src + gofs);
+            if (vec) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const pair_t v = *(gptr<const pair_t>)(f + (size_t)(r * R2) * est);
+                    re[r] = v.x;
+                    im[r] = v.y;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    re[r] = f[(size_t)(r * R2) * est];
+                    im[r] = f[(size_t)(r * R2) * est + po];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) x[r] = mk<C>((C)re[r], (C)im[r]);
+            Dft<C, R, -1>::run(x);
+            // (the factors after the transform: fetched before it they would
+            // hold as many registers again)
+            __builtin_amdgcn_sched_barrier(0);
+            split_twiddles<C, -1, R>(w, tw, p1);
+            C2<C> *o = buf + q1 * ls + p1 * js;
+#pragma unroll
+            for (int k = 0; k < R; ++k) o[k * ks] = k == 0 ? x[0] : cmul(x[k], w[k - 1]);
+        });
+    __syncthreads();
+    if (on2)
+        with_radix<RMAX>(R2, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<C> w[R], x[R];
+            C2<C> *o = buf + q2 * ls + p2 * ks;
+#pragma unroll
+            for (int j = 0; j < R; ++j) x[j] = o[j * js];
+            Dft<C, R, -1>::run(x);
+            // frequency k = k1 + R1 k2 times i s 2 pi m / L^2
+            const double k0 = 2.0 * 3.14159265358979323846 / ((double)L * (double)L) *
+                              ((MODE == 0 && !I.general) ? I.fdW[ax][ax] : 1.0);
+#pragma unroll
+            for (int k2 = 0; k2 < R; ++k2) {
+                const int k = p2 + R1 * k2;
+                const int m = 2 * k == L ? 0 : (2 * k < L ? k : k - L);
+                const C kap = (C)(k0 * (double)m);
+                x[k2] = mk<C>(-kap * x[k2].y, kap * x[k2].x);
+            }
+            Dft<C, R, 1>::run(x);
+            __builtin_amdgcn_sched_barrier(0);
+            split_twiddles<C, 1, R>(w, tw, p2);
+#pragma unroll
+            for (int j = 0; j < R; ++j) o[j * js] = j == 0 ? x[0] : cmul(x[j], w[j - 1]);
+        });
+    // (the divergence's potential so far is fetched across the barrier)
+    T *gout = reinterpret_cast<T *>(I.grad) + base + gofs;
+    T *vout = reinterpret_cast<T *>(I.v) + base + gofs;
+    const T *vin = rows ? reinterpret_cast<const T *>(I.vloc) + base + gofs : vout;
+    const bool vvec = MODE == 1 && pairable(vout) && pairable(vin), gvec = MODE == 0 && pairable(gout - gofs + ax * N);
+    __syncthreads();
+    if (on1)
+        with_radix<RMAX>(R1, [&](auto Rc) {
+            constexpr int R = decltype(Rc)::value;
+            C2<C> x[R];
+            T re[R], im[R];
+            if constexpr (MODE == 1) {
+                const gptr<const T> f = gld(vin);
+                if (vvec) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const pair_t v = *(gptr<const pair_t>)(f + (size_t)(r * R2) * est);
+                        re[r] = v.x;
+                        im[r] = v.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        re[r] = f[(size_t)(r * R2) * est];
+                        im[r] = f[(size_t)(r * R2) * est + po];
+                    }
+                }
+            }
+            const C2<C> *o = buf + q1 * ls + p1 * js;
+#pragma unroll
+            for (int k = 0; k < R; ++k) x[k] = o[k * ks];
+            Dft<C, R, 1>::run(x);
+            if (MODE == 0 && axis == 1 && I.general) {
+                // grad n = sum_c W[c] d_c n (the second value of a pair, then the first)
+                for (int h = po ? 1 : 0; h >= 0; --h) {
+                    const gptr<T> g = gst(gout + h * pst);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const size_t ofs = (size_t)(r * R2) * est;
+                        const double d1 = (double)(h ? x[r].y : x[r].x), d2 = (double)g[N + ofs], d3 = (double)g[2 * N + ofs];
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) g[c * N + ofs] = (T)(I.fdW[0][c] * d1 + I.fdW[1][c] * d2 + I.fdW[2][c] * d3);
+                    }
+                }
+                return;
+            }
+            const gptr<T> out = gst(MODE == 0 ? gout + ax * N : vout);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                re[r] = MODE == 0 ? (T)x[r].x : re[r] - (T)x[r].x;
+                im[r] = MODE == 0 ? (T)x[r].y : im[r] - (T)x[r].y;
+            }
+            if (MODE == 0 ? gvec : vvec) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) *(gptr<pair_t>)(out + (size_t)(r * R2) * est) = pair_t{re[r], im[r]};
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    out[(size_t)(r * R2) * est] = re[r];
+                    if (po) out[(size_t)(r * R2) * est + po] = im[r];
+                }
+            }
+        });
+}
+
 // spectra of nl lines (length L, pitch ls) times i s 2 pi m / L^2
 template <typename C>
 __device__ __forceinline__ void deriv_multiply(C2<C> *buf, int nl, int L, int ls, double s) {
@@ -662,72 +920,19 @@ __device__ __forceinline__ void deriv_multiply(C2<C> *buf, int nl, int L, int ls
     __syncthreads();
 }
 
-// Axis 3 (rows, contiguous).  tile: a = first row (i1 N2 + i2), b = rows
-// (even: rows 2p, 2p+1 form line p).  MODE 0: grad[2] = W[2][2] d_3 n
-// (orthorhombic) or d_3 n (general cells: the axis-1 pass combines); the
-// grid's first pass, it also clears the bad-density flag.  MODE 1: v =
-// v_loc - d_3 q_3 (q_3 in grad[2]).
-template <typename T, typename C, int LC, int V, int MODE>
-__global__ void __launch_bounds__(kThreads) k_drow(const InstDev *insts, const Tile *tiles, const void *twv) {
+// Axis 2 at a length without a split (the run-time radix passes).  tile: a =
+// i1, b = first i3, c = number W of consecutive i3 (pairs form one complex
+// line; an odd W's last line has a zero imaginary part).
+template <typename T, typename C, int MODE>
+__global__ void __launch_bounds__(kThreads) k_deriv_any(const InstDev *insts, const Tile *tiles, const void *twv) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Tile t = tiles[blockIdx.x];
     const InstDev &I = insts[t.inst];
-    const int N3 = axis_len<LC>(I.n3), row0 = t.a, B = t.b, np = B / 2, ls = N3 + 1;
+    constexpr int c = 1;                                       // lattice axis (0-based)
+    const int L = I.n2, lp = L | 1, Wc = t.c, np = (Wc + 1) / 2;
     const size_t N = (size_t)I.n1 * I.n2 * I.n3;
-    if (MODE == 0 && row0 == 0 && threadIdx.x == 0) gst(I.bad)[0] = 0;
-    C2<C> *tw = reinterpret_cast<C2<C> *>(smem);
-    C2<C> *buf = tw + N3;
-    const T *f = MODE == 0 ? reinterpret_cast<const T *>(I.n) + (size_t)row0 * N3
-                           : reinterpret_cast<const T *>(I.grad) + 2 * N + (size_t)row0 * N3;
-    batched<4>(np * N3, [&](int idx) {
-        const int pr = idx / N3, k = idx - pr * N3;
-        return mk<C>((C)gld(f)[(2 * pr) * N3 + k], (C)gld(f)[(2 * pr + 1) * N3 + k]);
-    }, [&](int idx, C2<C> z) {
-        const int pr = idx / N3, k = idx - pr * N3;
-        buf[pr * ls + k] = z;
-    });
-    load_twiddles<C>(tw, I.p3, reinterpret_cast<const C2<C> *>(twv));
-    __syncthreads();
-    fft_lc<C, -1, LC, V>(buf, I.p3, np, 1, ls, tw);
-    deriv_multiply<C>(buf, np, N3, ls, (MODE == 0 && !I.general) ? I.fdW[2][2] : 1.0);
-    fft_lc<C, 1, LC, V>(buf, I.p3, np, 1, ls, tw);
-    const int npt = B * N3;
-    if constexpr (MODE == 0) {
-        const gptr<T> g = gst(reinterpret_cast<T *>(I.grad) + 2 * N + (size_t)row0 * N3);
-        for (int idx = threadIdx.x; idx < npt; idx += kThreads) {
-            const int rb = idx / N3, k = idx - rb * N3;
-            const C2<C> z = buf[(rb >> 1) * ls + k];
-            g[idx] = (T)((rb & 1) ? z.y : z.x);
-        }
-    } else {
-        const gptr<const T> vl = gld(reinterpret_cast<const T *>(I.vloc) + (size_t)row0 * N3);
-        const gptr<T> v = gst(reinterpret_cast<T *>(I.v) + (size_t)row0 * N3);
-        batched<4>(npt, [&](int idx) { return vl[idx]; }, [&](int idx, T x) {
-            const int rb = idx / N3, k = idx - rb * N3;
-            const C2<C> z = buf[(rb >> 1) * ls + k];
-            v[idx] = x - (T)((rb & 1) ? z.y : z.x);
-        });
-    }
-}
-
-// Axes 2 (AX = 2: lines along i2, element stride N3) and 1 (AX = 1: along
-// i1, stride N2 N3).  tile: a = the other outer index (i1, or i2), b = first
-// i3, c = number W of consecutive i3 (pairs form one complex line; an odd
-// W's last line has a zero imaginary part).  MODE 0, AX = 2: grad[1] =
-// W[1][1] d_2 n (orthorhombic) or d_2 n (general).  MODE 0, AX = 1 (the last
-// gradient pass): grad[0] = W[0][0] d_1 n (orthorhombic); general cells: grad n
-// = sum_c W[c] d_c n from d_1 n and the stored d_2 n, d_3 n, all three
-// Cartesian components written.  MODE 1: v -= d_c q_c (q_c in grad[AX-1]).
-template <typename T, typename C, int LC, int V, int MODE, int AX>
-__global__ void __launch_bounds__(kThreads) k_dcol(const InstDev *insts, const Tile *tiles, const void *twv) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const Tile t = tiles[blockIdx.x];
-    const InstDev &I = insts[t.inst];
-    constexpr int c = AX - 1;                                  // lattice axis (0-based)
-    const int L = axis_len<LC>(AX == 2 ? I.n2 : I.n1), lp = L | 1, Wc = t.c, np = (Wc + 1) / 2;
-    const size_t N = (size_t)I.n1 * I.n2 * I.n3;
-    const int stride = AX == 2 ? I.n3 : I.n2 * I.n3;           // (32-bit offsets: 3 N < 2^31)
-    const size_t base = (AX == 2 ? (size_t)t.a * I.n2 * I.n3 : (size_t)t.a * I.n3) + t.b;
+    const int stride = I.n3;                                   // (32-bit offsets: 3 N < 2^31)
+    const size_t base = (size_t)t.a * I.n2 * I.n3 + t.b;
     C2<C> *tw = reinterpret_cast<C2<C> *>(smem);
     C2<C> *buf = tw + L;
     C *bc = reinterpret_cast<C *>(buf);                        // (re, im) of element e of line j / 2 at 2 ((j/2) lp + e) + j % 2
@@ -756,28 +961,16 @@ __global__ void __launch_bounds__(kThreads) k_dcol(const InstDev *insts, const T
     }
     if (Wc & 1)
         for (int e = threadIdx.x; e < L; e += kThreads) bc[2 * ((np - 1) * lp + e) + 1] = (C)0;
-    load_twiddles<C>(tw, AX == 2 ? I.p2 : I.p1, reinterpret_cast<const C2<C> *>(twv));
+    load_twiddles<C>(tw, I.p2, reinterpret_cast<const C2<C> *>(twv));
     __syncthreads();
-    fft_lc<C, -1, LC, V>(buf, AX == 2 ? I.p2 : I.p1, np, 1, lp, tw);
+    fft_lines<C>(buf, I.p2, np, 1, lp, tw, -1);
     deriv_multiply<C>(buf, np, L, lp, (MODE == 0 && !I.general) ? I.fdW[c][c] : 1.0);
-    fft_lc<C, 1, LC, V>(buf, AX == 2 ? I.p2 : I.p1, np, 1, lp, tw);
+    fft_lines<C>(buf, I.p2, np, 1, lp, tw, 1);
     T *gbase = reinterpret_cast<T *>(I.grad) + base;
     if constexpr (MODE == 0) {
-        const bool combine = AX == 1 && I.general;
         RowCursor cur(threadIdx.x, Wc);
-        for (int idx = threadIdx.x; idx < total; idx += kThreads, cur.step()) {
-            const int e = cur.l, j = cur.w;
-            const size_t o = (size_t)e * stride + j;
-            const C d = bc[2 * ((j >> 1) * lp + e) + (j & 1)];
-            if (!combine) {
-                gst(gbase)[c * N + o] = (T)d;
-            } else {
-                const double d1 = (double)d, d2 = (double)gld(gbase)[N + o], d3 = (double)gld(gbase)[2 * N + o];
-#pragma unroll
-                for (int x = 0; x < 3; ++x)
-                    gst(gbase)[x * N + o] = (T)(I.fdW[0][x] * d1 + I.fdW[1][x] * d2 + I.fdW[2][x] * d3);
-            }
-        }
+        for (int idx = threadIdx.x; idx < total; idx += kThreads, cur.step())
+            gst(gbase)[c * N + (size_t)cur.l * stride + cur.w] = (T)bc[2 * ((cur.w >> 1) * lp + cur.l) + (cur.w & 1)];
     } else {
         const gptr<T> v = gst(reinterpret_cast<T *>(I.v) + base);
         RowCursor cur(threadIdx.x, Wc);
@@ -801,26 +994,75 @@ __global__ void __launch_bounds__(kThreads) k_dcol(const InstDev *insts, const T
 
 // ---------------------------------------------------------------- axis-2 pass
 
+// E_k = (Omega/2) sum of the axis-1 partials; Delta E = dOmega sum of the
+// theta partials; E_x, E_c^LDA = dOmega sums of the semilocal partials (zero
+// unless the semilocal terms are on), into I.E[0..3]: NaN for a density the
+// theta pass flagged.  One workgroup, 256 running sums whatever its size (so
+// the summation order is the grid's own), eight loads in flight each.  These
+// are the first workgroups of the inverse axis-2 pass, beside its tiles: as a
+// launch of its own at the end, one workgroup a grid with one load in flight
+// per lane, the reduction took 4 us on 24^3, 25 us on 128^3 and 69 us on
+// 160 x 160 x 320.
+__device__ __forceinline__ void reduce_energies(const InstDev &I, double *acc) {
+    constexpr int V = 256, U = 8;
+    const int nt = blockDim.x, nq = I.semilocal ? 4 : 2;
+    for (int q = 0; q < nq; ++q) {
+        const int n = q == 0 ? I.n_ek : I.n_de, st = q < 2 ? 1 : 2;
+        const gptr<const double> p = gld(q == 0 ? I.part_ek : q == 1 ? I.part_de : I.part_sl + (q - 2));
+        for (int v = threadIdx.x; v < V; v += nt) {
+            double a = 0.0;
+            for (int i = v; i < n; i += U * V) {
+                double r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) r[u] = p[(size_t)min(i + u * V, n - 1) * st];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (i + u * V < n) a += r[u];
+            }
+            acc[q * V + v] = a;
+        }
+    }
+    for (int h = V / 2; h > 0; h >>= 1) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < h * nq; i += nt) {
+            const int q = i / h, v = i - q * h;
+            acc[q * V + v] += acc[q * V + v + h];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int q = threadIdx.x;
+        const double w = q == 0 ? 0.5 * I.omega : I.dvol;
+        gst(I.E)[q] = gld(I.bad)[0] != 0 ? __builtin_nan("") : q < nq ? w * acc[q * V] : 0.0;
+    }
+}
+
 // The 20 spectra along axis 2, lengths that split into two radices.  A tile is
-// kYC 16-byte chunks (256 contiguous bytes) of every row i2 of one plane:
+// kYC (16 or 8) 16-byte chunks of every row i2 of one plane:
 // step one loads its rows straight into registers (R1 16-byte loads in
 // flight per lane), step two stores its rows straight from them, and the
-// lines cross LDS once, conflict-free (16 lanes on consecutive chunks).  The
+// lines cross LDS once, conflict-free (lanes on consecutive chunks).  The
 // pass is bound by memory; crossing LDS at both ends and between the radix
 // passes, with divisions by run-time lengths outside eight lengths, had held
 // it below (with both passes changed, the evaluation of 96^3 in FP32 went
 // from 371 to 336 us, in FP64 from 565 to 518, of 90 x 100 x 108 from 653 to
 // 596, of 160 x 160 x 320 from 2337 to 2208).
 // tile: a = i1, b = first chunk of the row, c = chunks (<= kYC; the lanes
-// past them repeat the last one and store nothing).
+// past them repeat the last one and store nothing); a < 0 (inverse pass only):
+// the grid's energies.
 template <typename T, int S, int RMAX>
-__global__ void __launch_bounds__((kYC * RMAX + 63) / 64 * 64) k_y(const InstDev *insts, const Tile *tiles,
+__global__ void __launch_bounds__(kMaxThreads) k_y(const InstDev *insts, const Tile *tiles,
                                                                     const void *twv) {
     extern __shared__ __align__(16) unsigned char smem[];
     using K = Chunk<T>;
     using V = typename K::V;
+    constexpr int kYC = 1 << tile_lanes(RMAX);
     const Tile t = tiles[blockIdx.x];
     const InstDev &I = insts[t.inst];
+    if (S > 0 && t.a < 0) {
+        reduce_energies(I, reinterpret_cast<double *>(smem));
+        return;
+    }
     const int R1 = I.p2.r1, R2 = I.p2.r2;
     const size_t rowc = (size_t)I.n3h * (kNQ / K::N);          // chunks per row
     const int c = threadIdx.x % kYC, p = threadIdx.x / kYC;
@@ -885,6 +1127,10 @@ __global__ void __launch_bounds__(kThreads) k_y_any(const InstDev *insts, const 
     extern __shared__ __align__(16) unsigned char smem[];
     const Tile t = tiles[blockIdx.x];
     const InstDev &I = insts[t.inst];
+    if (S > 0 && t.a < 0) {
+        reduce_energies(I, reinterpret_cast<double *>(smem));
+        return;
+    }
     const int N2 = I.n2, W = t.c, lp = N2 | 1;                 // lines contiguous, odd pitch
     C2<T> *tw = reinterpret_cast<C2<T> *>(smem);
     C2<T> *buf = tw + N2;
@@ -893,7 +1139,7 @@ __global__ void __launch_bounds__(kThreads) k_y_any(const InstDev *insts, const 
     rows_in_t(buf, lp, g, rowlen, N2, W);
     load_twiddles<T>(tw, I.p2, reinterpret_cast<const C2<T> *>(twv));
     __syncthreads();
-    fft_lc<T, S, kLenGeneric, 0>(buf, I.p2, W, 1, lp, tw);
+    fft_lines<T>(buf, I.p2, W, 1, lp, tw, S);
     rows_out_t(g, rowlen, buf, lp, N2, W);
 }
 
@@ -904,19 +1150,6 @@ __global__ void __launch_bounds__(kThreads) k_y_any(const InstDev *insts, const 
 // and N2 - k2 share a kernel matrix; in general cells a matrix per k point,
 // as full rows or packed upper triangles, on the vector ALU.
 enum Contraction { CT_VEC = 0, CT_MFMA = 1, CT_GEN = 2, CT_GEN_PACKED = 3 };
-
-// Sum over the workgroup in a fixed order (any number of waves up to 8);
-// result valid in thread 0.
-__device__ __forceinline__ double block_sum_n(double v) {
-    __shared__ double red[8];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < ((int)blockDim.x + 63) / 64; ++w) s += red[w];
-    return s;
-}
 
 // Forward axis-1 FFT of the 20 theta spectra, u_a(G) = sum_b phi_ab(|G|) c_b(G)
 // with c = Theta / N (Eq. Eoffk, Eq. epsofk), the energy sum
@@ -950,7 +1183,7 @@ __device__ __forceinline__ double block_sum_n(double v) {
 // forward spectra c = FFT(theta)/N back in place of the tile (no contraction,
 // no inverse); 2 writes u = phi c (no inverse); 0 is the evaluation.
 template <typename T, int CT, int RMAX>
-__global__ void __launch_bounds__(sizeof(T) == 4 ? (20 * RMAX + 63) / 64 * 64 : 512)
+__global__ void __launch_bounds__(kMaxThreads, sizeof(T) == 4 ? (RMAX <= 16 ? 4 : RMAX <= 20 ? 3 : 2) : 1)
 k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *twv, int probe) {
     extern __shared__ __align__(16) unsigned char smem[];
     using Ch = Chunk<T>;
@@ -963,7 +1196,11 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
     const InstDev &I = insts[t.inst];
     const int N1 = I.n1, N2 = I.n2, N3 = I.n3, N3h = I.n3h, P = t.b, CP = t.c, K = P * CP;
     const int R1 = I.p1.r1, R2 = I.p1.r2;
-    const int nt = blockDim.x, C = K * kCpc;                   // chunks per slot
+    // the grid's own thread count (a launch has the largest of its grids'): the
+    // items of a thread, so the order of the energy sum, do not depend on the
+    // other grids of a batch; threads past it take no items
+    const int nt = I.zthreads, tid = (int)threadIdx.x < nt ? (int)threadIdx.x : 1 << 28;
+    const int C = K * kCpc;                                    // chunks per slot
     const int sb = K * kColB;                                  // bytes per slot
     const int s1 = R2 * sb + (((1 - R2) * sb) & 255);          // bytes per R2 slots: lanes C apart go on where C stop
     unsigned char *buf = smem;
@@ -983,13 +1220,14 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
     // the thread's first shell index is loaded before the tile (clamped,
     // unconditional) and stored after it
     auto smap_at = [&](int i) { return smap[(size_t)(i >> (P - 1)) * smap_m1 + (i & (P - 1))]; };
-    const int sh_first = smap_at(min((int)threadIdx.x, nitems - 1));
+    const int sh_first = smap_at(min(tid, nitems - 1));
 
+    const FastDiv byC{K == 2 ? div_magic(2 * kCpc) : div_magic(kCpc)}, byR1{I.p1.d1};
     // step one of the forward transform: rows -> registers -> slots
-    for (int it = threadIdx.x; it < C * R2; it += nt) {
-        const int p = it / C, c = it - p * C, w = c / kCpc, e = c - w * kCpc;
+    for (int it = tid; it < C * R2; it += nt) {
+        const int p = byC(it), c = it - __mul24(p, C), w = c / kCpc, e = c - w * kCpc;
         const V *g = reinterpret_cast<const V *>((w ? col1 : col0) + (size_t)p * plane) + e;
-        unsigned char *lb = buf + p * sb + c * 16;
+        unsigned char *lb = buf + __mul24(p, sb) + c * 16;
         const size_t step = (size_t)R2 * plane * sizeof(C2<T>);
         with_radix<RMAX>(R1, [&](auto Rc) {
             constexpr int R = decltype(Rc)::value;
@@ -1016,14 +1254,14 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
             }
         });
     }
-    for (int k = threadIdx.x; k < N1; k += nt) {
-        const int q = k / R1;
+    for (int k = tid; k < N1; k += nt) {
+        const int q = byR1(k);
         soff[k] = (k - q * R1) * s1 + q * sb;
     }
-    if ((int)threadIdx.x < nitems) sidx[threadIdx.x] = sh_first;
-    for (int i = threadIdx.x + nt; i < nitems; i += nt) sidx[i] = smap_at(i);
+    if (tid < nitems) sidx[tid] = sh_first;
+    for (int i = tid + nt; i < nitems; i += nt) sidx[i] = smap_at(i);
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ngroups = (nt >> 6) * (64 / kNQ);
+    const int lane = threadIdx.x & 63, wave = tid >> 6, ngroups = (nt >> 6) * (64 / kNQ);
     const int grp = lane / kNQ, al = lane - grp * kNQ;
     const bool lane_on = grp < 64 / kNQ;
     const int gid = wave * (64 / kNQ) + grp;
@@ -1070,9 +1308,9 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
     const int it0 = MF ? wave * (64 / kNQ) + mf_g : gid;
     if (MF || lane_on) fetch(it0, fa);
     // step two: the slots of (chunk, k1), in place
-    for (int it = threadIdx.x; it < C * R1; it += nt) {
-        const int p = it / C, c = it - p * C;
-        unsigned char *lb = buf + p * s1 + c * 16;
+    for (int it = tid; it < C * R1; it += nt) {
+        const int p = byC(it), c = it - __mul24(p, C);
+        unsigned char *lb = buf + __mul24(p, s1) + c * 16;
         with_radix<RMAX>(R2, [&](auto Rc) {
             constexpr int R = decltype(Rc)::value;
             C2<T> x[Ch::N][R];
@@ -1098,8 +1336,8 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
 
     // (probes) the tile's spectrum to its rows
     auto store_spectrum = [&](T scale) {
-        for (int it = threadIdx.x; it < C * N1; it += nt) {
-            const int k = it / C, c = it - k * C, w = c / kCpc, e = c - w * kCpc;
+        for (int it = tid; it < C * N1; it += nt) {
+            const int k = byC(it), c = it - __mul24(k, C), w = c / kCpc, e = c - w * kCpc;
             C2<T> a[Ch::N];
             Ch::split(*reinterpret_cast<const V *>(buf + soff[k] + c * 16), a);
             for (int q = 0; q < Ch::N; ++q) a[q] = cscale(a[q], scale);
@@ -1244,9 +1482,9 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
         return;
     }
     // the inverse transform: step two backwards, in place
-    for (int it = threadIdx.x; it < C * R1; it += nt) {
-        const int p = it / C, c = it - p * C;
-        unsigned char *lb = buf + p * s1 + c * 16;
+    for (int it = tid; it < C * R1; it += nt) {
+        const int p = byC(it), c = it - __mul24(p, C);
+        unsigned char *lb = buf + __mul24(p, s1) + c * 16;
         with_radix<RMAX>(R2, [&](auto Rc) {
             constexpr int R = decltype(Rc)::value;
             C2<T> tf[R], x[Ch::N][R];
@@ -1271,10 +1509,10 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
     }
     __syncthreads();
     // and step one: slots -> registers -> rows
-    for (int it = threadIdx.x; it < C * R2; it += nt) {
-        const int p = it / C, c = it - p * C, w = c / kCpc, q0 = c - w * kCpc;
+    for (int it = tid; it < C * R2; it += nt) {
+        const int p = byC(it), c = it - __mul24(p, C), w = c / kCpc, q0 = c - w * kCpc;
         V *g = reinterpret_cast<V *>((w ? col1 : col0) + (size_t)p * plane) + q0;
-        const unsigned char *lb = buf + p * sb + c * 16;
+        const unsigned char *lb = buf + __mul24(p, sb) + c * 16;
         const size_t step = (size_t)R2 * plane * sizeof(C2<T>);
         with_radix<RMAX>(R1, [&](auto Rc) {
             constexpr int R = decltype(Rc)::value;
@@ -1297,7 +1535,7 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
             }
         });
     }
-    const double sum = block_sum_n(e);
+    const double sum = block_sum(e);
     if (threadIdx.x == 0) I.part_ek[t.slot] = sum;
 }
 
@@ -1311,7 +1549,7 @@ k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *
 // points into dst [kNQ][N] (working precision), from n and the stored grad n,
 // as the theta pass forms them.  tile: a = first row, b = rows.
 template <typename T>
-__global__ void __launch_bounds__(kThreads) k_probe_theta(const InstDev *insts, const Tile *tiles,
+__global__ void __launch_bounds__(kMaxThreads) k_probe_theta(const InstDev *insts, const Tile *tiles,
                                                           const Consts *cst, void *dstv, int target) {
     __shared__ T qm[kNQ], Mm[kNQ * kNQ], invm[kMaxMc + 1];
     const Tile t = tiles[blockIdx.x];
@@ -1324,7 +1562,7 @@ __global__ void __launch_bounds__(kThreads) k_probe_theta(const InstDev *insts, 
     const T *nin = reinterpret_cast<const T *>(I.n) + p0;
     const T *gin = reinterpret_cast<const T *>(I.grad) + p0;
     T *dst = reinterpret_cast<T *>(dstv) + p0;
-    for (int idx = threadIdx.x; idx < t.b * N3; idx += kThreads) {
+    for (int idx = threadIdx.x; idx < t.b * N3; idx += blockDim.x) {
         const T nv = nin[idx];
         T th[kNQ];
 #pragma unroll
@@ -1352,25 +1590,25 @@ __global__ void __launch_bounds__(kThreads) k_probe_theta(const InstDev *insts, 
 // u_a(r_i) = sum_G u_a(G) exp(i G.r_i) (Eq. (epsilon)): the inverse axis-3
 // transform of the u spectra, as the assembly pass forms it, into dst
 // [kNQ][N] (working precision).  tile: a = first row, b = rows.
-template <typename T, int LC, int V>
-__global__ void __launch_bounds__(kThreads) k_probe_u(const InstDev *insts, const Tile *tiles, const void *twv,
-                                                      void *dstv, int target) {
+template <typename T, int RMAX>
+__global__ void __launch_bounds__(kMaxThreads) k_probe_u(const InstDev *insts, const Tile *tiles, const void *twv,
+                                                        void *dstv, int target) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Tile t = tiles[blockIdx.x];
     if (t.inst != target) return;
     const InstDev &I = insts[t.inst];
-    const int N3 = axis_len<LC>(I.n3), N3h = N3 / 2 + 1, row0 = t.a, B = t.b, ls = N3 + 1;
+    const XTile<T, 0, 0> X(I.p3);
+    const int N3 = X.len(), N3h = N3 / 2 + 1, row0 = t.a, B = t.b, nt = blockDim.x;
     const size_t N = (size_t)I.n1 * I.n2 * I.n3;
-    C2<T> *r2 = reinterpret_cast<C2<T> *>(smem);
-    C2<T> *tw = r2 + kNQ / 2 * B * ls;
-    u_lines_in<T>(r2, ls, reinterpret_cast<const C2<T> *>(I.spec) + (size_t)row0 * N3h * kNQ, B, N3, N3h);
+    C2<T> *tw = reinterpret_cast<C2<T> *>(smem + B * X.rs());
     load_twiddles<T>(tw, I.p3, reinterpret_cast<const C2<T> *>(twv));
+    u_lines_in(smem, X, reinterpret_cast<const C2<T> *>(I.spec) + (size_t)row0 * N3h * kNQ, B, I.dn3h);
     __syncthreads();
-    fft_lc<T, 1, LC, V>(r2, I.p3, kNQ / 2 * B, 1, ls, tw);
+    xtile_fft<T, 1, RMAX, 0, 0>(smem, X, B, tw);
     T *dst = reinterpret_cast<T *>(dstv) + (size_t)row0 * N3;
-    for (int idx = threadIdx.x; idx < (kNQ / 2) * B * N3; idx += kThreads) {
+    for (int idx = threadIdx.x; idx < (kNQ / 2) * B * N3; idx += nt) {
         const int m = idx / (B * N3), rest = idx - m * B * N3, rb = rest / N3, k = rest - rb * N3;
-        const C2<T> z = r2[(kNQ / 2 * rb + m) * ls + k];
+        const C2<T> z = reinterpret_cast<const C2<T> *>(smem + __mul24(rb, X.rs()) + X.elem(k))[m];
         dst[(size_t)(2 * m) * N + rest] = z.x;
         dst[(size_t)(2 * m + 1) * N + rest] = z.y;
     }
@@ -1398,28 +1636,57 @@ static void allow_lds(K kernel, size_t bytes) {
                                 __VA_ARGS__);                                                        \
     } while (0)
 
-template <typename T, int LC, int V>
-hipError_t launch_x_lc(int kind, const LaunchArgs &a) {
+// the axis-3 passes: by split class, or as a compile-time length
+template <typename T, int RMAX, int CR1, int CR2>
+hipError_t launch_x_pass(int kind, const LaunchArgs &a) {
     switch (kind) {
-        // (the gradient's one-axis transforms in FP64, the divergence's in T)
-        case KG_X: VDWNL_LAUNCH((k_drow<T, double, LC, V, 0>), a.twd); break;
-        case KD_X: VDWNL_LAUNCH((k_drow<T, T, LC, V, 1>), a.tw); break;
-        case KX_THETA: VDWNL_LAUNCH((k_x_theta<T, LC, V>), a.cst, a.tw); break;
-        case KX_ASSEMBLE: VDWNL_LAUNCH((k_x_assemble<T, LC, V>), a.cst, a.tw); break;
-        case KP_U: VDWNL_LAUNCH((k_probe_u<T, LC, V>), a.tw, a.dst, a.target); break;
+        case KX_THETA: VDWNL_LAUNCH((k_x_theta<T, RMAX, CR1, CR2>), a.cst, a.tw); break;
+        case KX_ASSEMBLE: VDWNL_LAUNCH((k_x_assemble<T, RMAX, CR1, CR2>), a.cst, a.tw); break;
+        case KP_U: VDWNL_LAUNCH((k_probe_u<T, RMAX>), a.tw, a.dst, a.target); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
-
-template <typename T, int LC, int V>
-hipError_t launch_y_lc(int kind, const LaunchArgs &a) {
-    switch (kind) {
-        case KG_Y: VDWNL_LAUNCH((k_dcol<T, double, LC, V, 0, 2>), a.twd); break;
-        case KD_Y: VDWNL_LAUNCH((k_dcol<T, T, LC, V, 1, 2>), a.tw); break;
+template <typename T>
+hipError_t launch_x(int kind, int cls, const LaunchArgs &a) {
+    switch (a.len) {
+        case 24: return launch_x_pass<T, 10, 4, 6>(kind, a);
+        case 32: return launch_x_pass<T, 10, 4, 8>(kind, a);
+        case 48: return launch_x_pass<T, 10, 6, 8>(kind, a);
+        case 64: return launch_x_pass<T, 10, 8, 8>(kind, a);
+        case 96: return launch_x_pass<T, 16, 8, 12>(kind, a);
+        case 128: return launch_x_pass<T, 16, 8, 16>(kind, a);
+        case 160: return launch_x_pass<T, 16, 10, 16>(kind, a);
+        case 320: return launch_x_pass<T, 20, 16, 20>(kind, a);
+        default: break;
+    }
+    switch (cls) {
+        case 0: return launch_x_pass<T, kSplitClassMax[0], 0, 0>(kind, a);
+        case 1: return launch_x_pass<T, kSplitClassMax[1], 0, 0>(kind, a);
+        case 2: return launch_x_pass<T, kSplitClassMax[2], 0, 0>(kind, a);
+        case 3: return launch_x_pass<T, kSplitClassMax[3], 0, 0>(kind, a);
         default: return hipErrorInvalidValue;
     }
+}
+
+// the one-axis derivatives: by split class (the gradient's transforms in FP64,
+// the divergence's in T); kLenGeneric: axis 2 without a split
+template <typename T, typename C, int MODE>
+hipError_t launch_deriv(int cls, const LaunchArgs &a) {
+    const void *tw = MODE == 0 ? a.twd : a.tw;
+    switch (cls) {
+        case 0: VDWNL_LAUNCH((k_deriv<T, C, kSplitClassMax[0], MODE>), tw); break;
+        case 1: VDWNL_LAUNCH((k_deriv<T, C, kSplitClassMax[1], MODE>), tw); break;
+        case 2: VDWNL_LAUNCH((k_deriv<T, C, kSplitClassMax[2], MODE>), tw); break;
+        case 3: VDWNL_LAUNCH((k_deriv<T, C, kSplitClassMax[3], MODE>), tw); break;
+        default: VDWNL_LAUNCH((k_deriv_any<T, C, MODE>), tw); break;
+    }
     return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_deriv(int kind, int cls, const LaunchArgs &a) {
+    const bool grad = kind == KG_X || kind == KG_Y || kind == KG_Z;
+    return grad ? launch_deriv<T, double, 0>(cls, a) : launch_deriv<T, T, 1>(cls, a);
 }
 
 // the axis-2 passes of the 20 spectra: by split class
@@ -1429,17 +1696,8 @@ hipError_t launch_y20(int cls, const LaunchArgs &a) {
         case 0: VDWNL_LAUNCH((k_y<T, S, kSplitClassMax[0]>), a.tw); break;
         case 1: VDWNL_LAUNCH((k_y<T, S, kSplitClassMax[1]>), a.tw); break;
         case 2: VDWNL_LAUNCH((k_y<T, S, kSplitClassMax[2]>), a.tw); break;
+        case 3: VDWNL_LAUNCH((k_y<T, S, kSplitClassMax[3]>), a.tw); break;
         default: VDWNL_LAUNCH((k_y_any<T, S>), a.tw); break;
-    }
-    return hipGetLastError();
-}
-
-template <typename T, int LC, int V>
-hipError_t launch_z_lc(int kind, const LaunchArgs &a) {
-    switch (kind) {
-        case KG_Z: VDWNL_LAUNCH((k_dcol<T, double, LC, V, 0, 1>), a.twd); break;
-        case KD_Z: VDWNL_LAUNCH((k_dcol<T, T, LC, V, 1, 1>), a.tw); break;
-        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
@@ -1451,6 +1709,7 @@ hipError_t launch_zmain(int cls, int probe, const LaunchArgs &a) {
         case 0: VDWNL_LAUNCH((k_z_main<T, CT, kZClassMax[0]>), a.cols, a.tw, probe); break;
         case 1: VDWNL_LAUNCH((k_z_main<T, CT, kZClassMax[1]>), a.cols, a.tw, probe); break;
         case 2: VDWNL_LAUNCH((k_z_main<T, CT, kZClassMax[2]>), a.cols, a.tw, probe); break;
+        case 3: VDWNL_LAUNCH((k_z_main<T, CT, kZClassMax[3]>), a.cols, a.tw, probe); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1464,28 +1723,5 @@ hipError_t launch_zmain(int cls, int probe, const LaunchArgs &a) {
 }
 
 #undef VDWNL_LAUNCH
-
-// (length class, radix order) at run time -> the compiled instance; an order
-// beyond the class's variants takes its last one
-#define VDWNL_LC_VARIANTS(FN, T, kind, lc, var, a)                                                        \
-    switch (lc) {                                                                                         \
-        case 0: return FN<T, 0, 0>(kind, a);                                                              \
-        case 1: return (var) >= 1 ? FN<T, 1, 1>(kind, a) : FN<T, 1, 0>(kind, a);                          \
-        case 2: return (var) >= 1 ? FN<T, 2, 1>(kind, a) : FN<T, 2, 0>(kind, a);                          \
-        case 3:                                                                                           \
-            return (var) >= 3 ? FN<T, 3, 3>(kind, a)                                                      \
-                   : (var) == 2 ? FN<T, 3, 2>(kind, a)                                                    \
-                   : (var) == 1 ? FN<T, 3, 1>(kind, a) : FN<T, 3, 0>(kind, a);                            \
-        case 4: return (var) >= 2 ? FN<T, 4, 2>(kind, a) : (var) == 1 ? FN<T, 4, 1>(kind, a) : FN<T, 4, 0>(kind, a); \
-        case 5:                                                                                           \
-            return (var) >= 5 ? FN<T, 5, 5>(kind, a)                                                      \
-                   : (var) == 4 ? FN<T, 5, 4>(kind, a)                                                    \
-                   : (var) == 3 ? FN<T, 5, 3>(kind, a)                                                    \
-                   : (var) == 2 ? FN<T, 5, 2>(kind, a)                                                    \
-                   : (var) == 1 ? FN<T, 5, 1>(kind, a) : FN<T, 5, 0>(kind, a);                            \
-        case 6: return (var) >= 1 ? FN<T, 6, 1>(kind, a) : FN<T, 6, 0>(kind, a);                          \
-        case 7: return (var) >= 1 ? FN<T, 7, 1>(kind, a) : FN<T, 7, 0>(kind, a);                          \
-        default: return FN<T, kLenGeneric, 0>(kind, a);                                                   \
-    }
 
 }  // namespace vdwnl

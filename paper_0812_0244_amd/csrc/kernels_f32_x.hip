@@ -1,11 +1,9 @@
-// Axis-3 passes (theta, assembly, the n and divergence transforms, the u probe) of the FP32 evaluation, every length class and radix order (see
-// kernels.hpp).
+// Axis-3 passes (theta, assembly, the u probe) of the FP32 evaluation, every split
+// class (see kernels.hpp).
 #include "kernels.hpp"
 
 namespace vdwnl {
 
-hipError_t launch_x_f32(int kind, int lc, int var, const LaunchArgs &a) {
-    VDWNL_LC_VARIANTS(launch_x_lc, float, kind, lc, var, a)
-}
+hipError_t launch_x_f32(int kind, int cls, const LaunchArgs &a) { return launch_x<float>(kind, cls, a); }
 
 }  // namespace vdwnl

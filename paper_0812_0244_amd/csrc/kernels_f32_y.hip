@@ -1,13 +1,13 @@
-// Axis-2 passes of the FP32 evaluation, every length class and radix order (see
-// kernels.hpp).
+// Axis-2 passes of the 20 spectra and the one-axis derivatives of the FP32
+// evaluation, every split class (see kernels.hpp).
 #include "kernels.hpp"
 
 namespace vdwnl {
 
-hipError_t launch_y_f32(int kind, int lc, int var, const LaunchArgs &a) {
-    if (kind == KY_20F) return launch_y20<float, -1>(lc, a);
-    if (kind == KY_20I) return launch_y20<float, 1>(lc, a);
-    VDWNL_LC_VARIANTS(launch_y_lc, float, kind, lc, var, a)
+hipError_t launch_y_f32(int kind, int cls, const LaunchArgs &a) {
+    if (kind == KY_20F) return launch_y20<float, -1>(cls, a);
+    if (kind == KY_20I) return launch_y20<float, 1>(cls, a);
+    return launch_deriv<float>(kind, cls, a);
 }
 
 }  // namespace vdwnl

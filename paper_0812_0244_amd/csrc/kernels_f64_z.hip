@@ -1,14 +1,10 @@
-// Axis-1 passes (the fused contraction pass, the gradient and divergence multipliers, the spectra probes) of the FP64 evaluation, every length class and radix order (see
-// kernels.hpp).
+// Fused axis-1 pass of the FP64 evaluation, every split class (see kernels.hpp).
 #include "kernels.hpp"
 
 namespace vdwnl {
 
-hipError_t launch_z_f64(int kind, int lc, int var, const LaunchArgs &a) {
-    if (kind == KZ_MAIN) return launch_zmain<double>(lc, 0, a);
-    if (kind == KP_THETA_K) return launch_zmain<double>(lc, 1, a);
-    if (kind == KP_U_K) return launch_zmain<double>(lc, 2, a);
-    VDWNL_LC_VARIANTS(launch_z_lc, double, kind, lc, var, a)
+hipError_t launch_z_f64(int kind, int cls, const LaunchArgs &a) {
+    return launch_zmain<double>(cls, kind == KP_THETA_K ? 1 : kind == KP_U_K ? 2 : 0, a);
 }
 
 }  // namespace vdwnl
