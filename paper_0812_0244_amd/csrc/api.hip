@@ -524,9 +524,13 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     // lengths without a split), bounded by their per-thread register arrays
     auto cap = [](size_t) { return (size_t)kTileCap; };
     g.bmain = xpass_rows(g, rs, c->pref[TG_X]);
-    // rows of a stencil tile: about 4096 points
-    g.bnf = 2;
-    while ((size_t)(g.bnf + 2) * N3 <= 4096) g.bnf += 2;
+    // rows of a stencil tile: 256 to 4096 points, some 1024 tiles per grid where
+    // it has the points (48^3 ran 28 workgroups of 4096 points, a ninth of the
+    // CUs: the two passes took 15 + 18 us, 7 + 7 now)
+    {
+        const size_t pts = std::min<size_t>(4096, std::max<size_t>(256, N1 * N2 * N3 / 1024));
+        g.bnf = (int)std::max<size_t>(1, std::min<size_t>(pts / N3, N1 * N2));
+    }
     // fused axis-1 tiles: two columns (a pair k2, N2 - k2 shares its kernel
     // rows) where they fit the budget; in FP64, whose columns are twice as
     // large, only up to 16 KB: a second workgroup per CU is worth more than the
