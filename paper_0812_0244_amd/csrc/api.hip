@@ -249,7 +249,8 @@ struct vdwnl_ctx {
     std::vector<hipStream_t> chain_streams;   // one per group (graph capture)
     std::vector<hipEvent_t> chain_events;     // fork (index 0) and one join per group
     double *h_E = nullptr;                // pinned
-    std::map<int, int> tw_off;            // length -> offset
+    std::map<int, int> tw_off;            // length -> offset of its twiddles
+    std::map<int, int> dw_off;            // and of its derivative weights
     // the evaluation captured as a HIP graph (replayed on the caller's stream)
     bool use_graph = true;
     hipStream_t cap_stream = nullptr;
@@ -514,6 +515,15 @@ static int zmain_threads(const Grid &g, int K, size_t cs) {
     return std::min((items + 63) / 64 * 64, kMaxThreads);
 }
 
+// The divergence (and the gradient in general cells, which otherwise takes
+// two launches) as direct sums over each axis, one launch, instead of
+// transforms, whose three passes each update the potential: edges to
+// kDenseMax.  24^3 in FP64 83 -> 75 us per evaluation; at 48^3 the sums' work
+// (N terms a point and axis) already takes the launches' place (triclinic FP64
+// 154 -> 152, 24 grids of edges 24 to 48 309 -> 365 us if all took it, 309 ->
+// 302 with edges to 32).
+static bool dense_deriv(const Grid &g) { return std::max(g.s[0], std::max(g.s[1], g.s[2])) <= kDenseMax; }
+
 // Tile shapes of grid g from the LDS budget of each pass group: each tile as
 // large as the FFT tile cap and its group's budget allow (at least one unit).
 static void size_tiles(const vdwnl_ctx *c, Grid &g) {
@@ -524,7 +534,7 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     // lengths without a split), bounded by their per-thread register arrays
     auto cap = [](size_t) { return (size_t)kTileCap; };
     g.bmain = xpass_rows(g, rs, c->pref[TG_X]);
-    // rows of a stencil tile: 256 to 4096 points, some 1024 tiles per grid where
+    // rows of a stencil (or direct-sum derivative) tile: 256 to 4096 points, some 1024 tiles per grid where
     // it has the points (48^3 ran 28 workgroups of 4096 points, a ninth of the
     // CUs: the two passes took 15 + 18 us, 7 + 7 now)
     {
@@ -855,9 +865,9 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
         for (int k = 0; k < KIND_COUNT; ++k) first_tile[k] = tiles[k].size();
         // runs of lines of the stencil passes; or the tiles of the one-axis
         // derivatives (slot = the axis)
-        if (c->grad_mode > 0) {
+        if (c->grad_mode > 0 || dense_deriv(g))
             for (int r = 0; r < rows; r += g.bnf) tiles[KF_GRAD].push_back({inst, r, std::min(g.bnf, rows - r), 0, -1});
-        } else {
+        if (c->grad_mode == 0) {
             const int w1 = 2 << tile_lanes(g.p1.r2), w3 = 2 << tile_lanes(g.p3.r2);
             const int w2 = y_class(c, g) != kLenGeneric ? 2 << tile_lanes(g.p2.r2) : g.wdy;
             for (int i1 = 0; i1 < N1; ++i1)
@@ -974,7 +984,7 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
             // fused pass's general variant, full or packed rows)
             const int cls = (std::min(split_class(g.s[0]), 4) * 5 + std::min(y_class(c, g), 4)) * 5 + split_class(g.s[2]);
             // (lengths of axis 3 with a compile-time kernel: groups of their own)
-            const int key = (cls * kNumLenClasses + len_class(g.s[2])) * 4 + (g.general ? 1 : 0) + (c->shells[g.shell_key].packed ? 2 : 0);
+            const int key = ((cls * 2 + (dense_deriv(g) ? 1 : 0)) * kNumLenClasses + len_class(g.s[2])) * 4 + (g.general ? 1 : 0) + (c->shells[g.shell_key].packed ? 2 : 0);
             auto it = std::find(keys.begin(), keys.end(), key);
             group_of[gi] = (int)(it - keys.begin());
             if (it == keys.end()) keys.push_back(key);
@@ -1064,6 +1074,7 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
                 add(KF_GRAD, off[KF_GRAD], cnt[KF_GRAD], 0, {KF_GRAD});
                 add(KF_DIV, off[KF_GRAD], cnt[KF_GRAD], 0, {KF_GRAD});
             } else {
+                const bool dense = dense_deriv(g0);
                 // gradient: the three directions are independent (one launch),
                 // but in general cells the axis-1 pass combines them
                 if (!split2) add(KG_Y, off[KD_Y], cnt[KD_Y], kLenGeneric, {KG_Y});
@@ -1071,14 +1082,20 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
                 if (!g0.general) {
                     if (split2) add(KG_X, off[lo], n2 + cnt[KD_X] + cnt[KD_Z], c123, {KG_X, KG_Y, KG_Z});
                     else add(KG_X, off[lo], cnt[KD_X] + cnt[KD_Z], c13, {KG_X, KG_Z});
+                } else if (dense) {
+                    add(KG_X, off[KF_GRAD], cnt[KF_GRAD], kDenseClass, {KF_GRAD});
                 } else {
                     if (split2) add(KG_X, off[lo], n2 + cnt[KD_X], std::max(c2, c3), {KG_X, KG_Y});
                     else add(KG_X, off[lo], cnt[KD_X], c3, {KG_X});
                     add(KG_Z, off[KD_Z], cnt[KD_Z], c1, {KG_Z});
                 }
-                add(KD_X, off[KD_X], cnt[KD_X], c3, {KD_X});
-                add(KD_Y, off[KD_Y], cnt[KD_Y], c2, {KD_Y});
-                add(KD_Z, off[KD_Z], cnt[KD_Z], c1, {KD_Z});
+                if (dense) {
+                    add(KD_X, off[KF_GRAD], cnt[KF_GRAD], kDenseClass, {KF_GRAD});
+                } else {
+                    add(KD_X, off[KD_X], cnt[KD_X], c3, {KD_X});
+                    add(KD_Y, off[KD_Y], cnt[KD_Y], c2, {KD_Y});
+                    add(KD_Z, off[KD_Z], cnt[KD_Z], c1, {KD_Z});
+                }
             }
             add(KX_THETA, off[KX_THETA], cnt[KX_THETA], c3, {KX_THETA});
             add(KY_20F, off[KY_20F], cnt[KY_20F], c2, {KY_20F});
@@ -1089,6 +1106,7 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
     }
     // twiddles
     c->tw_off.clear();
+    c->dw_off.clear();
     std::vector<double> twd;
     for (auto &g : c->grids)
         for (FftPlan *p : {&g.p1, &g.p2, &g.p3}) {
@@ -1103,9 +1121,19 @@ static int build_image(vdwnl_ctx *c, Image &im, bool keep_tables) {
                     twd.push_back(-std::sin(ang));
                 }
                 p->tw = o;
+                // weights of the direct-sum derivative (padded to whole pairs)
+                if (p->n <= kDenseMax) {
+                    const int h = (p->n - 1) / 2;
+                    c->dw_off[p->n] = (int)twd.size();
+                    for (int m = 1; m <= h + (h & 1); ++m) {
+                        const double a = M_PI * m / p->n, sg = (m & 1 ? M_PI : -M_PI) / p->n;
+                        twd.push_back(m > h ? 0.0 : p->n % 2 ? sg / std::sin(a) : sg * std::cos(a) / std::sin(a));
+                    }
+                }
             } else {
                 p->tw = it->second;
             }
+            p->dw = p->n <= kDenseMax ? c->dw_off[p->n] : 0;
         }
     // the rest of the buffer
     im.ws = off;

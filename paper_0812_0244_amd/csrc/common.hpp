@@ -15,6 +15,8 @@ constexpr size_t kFullRowCacheBytes = (size_t)256 << 20;   // a general-cell tab
 constexpr int kThreads = 256;                    // threads per workgroup, every kernel
 constexpr int kTileCap = 4096;                   // complex elements of one LDS FFT tile
 constexpr int kLdsCap = 65536;                   // bytes of LDS one workgroup may take
+constexpr int kDenseMax = 32;                    // longest edge of grids whose divergence is a direct sum
+constexpr int kDenseClass = 16;                  // launch class of those derivatives
 constexpr size_t kReduceLds = 4 * 256 * sizeof(double);   // running sums of the energy reduction
 constexpr int kMaxStages = 16;
 // Most threads of a workgroup.  Five to seven waves do not spread evenly over
@@ -35,6 +37,7 @@ struct FftPlan {
     int tw;
     int r1, r2;              // the length as two radices (fft_split.hpp), 0 where it has no such split
     uint32_t d1, d2, dn;     // div_magic of r1, r2 and n
+    int dw;                  // offset of its derivative weights in the twiddle table (real values; n <= kDenseMax)
 };
 
 // Per-grid state seen by the kernels.  Field layouts (C order):
