@@ -227,6 +227,7 @@ struct vdwnl_ctx {
     // when the plan fits its scratch buffer (with the kernel rows)
     Image img;
     bool img_valid = false;
+    bool img_built = false;               // img holds the plan's tiles and launches (the kernel rows only if img_valid)
     size_t img_need = 0;                  // bytes of the plan's image (0: no plan)
     uint64_t plan_stamp = 0;              // changes whenever the image does
     std::vector<InstDev> na_inst;         // instance table of the no-allocation entry point
@@ -1312,9 +1313,14 @@ static int prepare_device(vdwnl_ctx *c) {
     free_device(c);
     Image tmp;
     const Image *im = &c->img;
-    if (!c->img_valid) {
+    if (!c->img_built) {
         int rc = build_image(c, tmp, false);
         if (rc != VDWNL_OK) return rc;
+        im = &tmp;
+    } else if (!c->img_valid) {
+        tmp = std::move(c->img);
+        c->img = Image();
+        c->img_built = false;
         im = &tmp;
     }
     int rc = lds_optin(c);
@@ -1620,7 +1626,7 @@ static hipError_t scratch_setup(int device) {
 // (with its kernel rows) only when the whole image fits the scratch buffer.
 static void refresh_image(vdwnl_ctx *c) {
     c->img = Image();
-    c->img_valid = false;
+    c->img_valid = c->img_built = false;
     c->img_need = 0;
     {
         std::lock_guard<std::mutex> lk(g_stamp_mu);
@@ -1648,8 +1654,14 @@ static void refresh_image(vdwnl_ctx *c) {
         }
     }
     c->img_need = probe.total;
-    if (probe.total > kScratchBytes) return;
+    if (probe.total > kScratchBytes) {
+        // (kept for the first evaluation's upload, which then lets it go)
+        c->img = std::move(probe);
+        c->img_built = true;
+        return;
+    }
     if (build_image(c, c->img, true) != VDWNL_OK) return;
+    c->img_built = true;
     c->na_inst.assign(c->grids.size(), InstDev());
     c->na_E.assign(4 * c->grids.size(), 0.0);
     c->img_valid = true;
@@ -1984,7 +1996,7 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
     for (size_t b : {16384, 24576, 32768, 49152, 65536, 98304, 131072})
         if (b <= ctx->lds_cap) cand.push_back(b);
     const bool timing0 = ctx->timing;
-    ctx->img_valid = false;     // (the candidates' tiles differ from the image's)
+    ctx->img_valid = ctx->img_built = false;     // (the candidates' tiles differ from the image's)
     for (auto &x : ctx->variant) x = 0;
     // contraction units to try: the vector ALU, and the matrix cores where
     // some grid takes them (FP32, orthorhombic cell)
