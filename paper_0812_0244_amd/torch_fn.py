@@ -86,9 +86,10 @@ class VdwNlEnergy(torch.autograd.Function):
         e, v = engine.total(n.detach())
         ctx.save_for_backward(v)
         ctx.dvol = engine.dvol
-        return torch.tensor(e, dtype=torch.float64, device=n.device)
+        # (a fill on the stream: a tensor made from a host number is a copy that waits)
+        return torch.full((), e, dtype=torch.float64, device=n.device)
 
     @staticmethod
     def backward(ctx, gE):
         (v,) = ctx.saved_tensors
-        return (gE.to(v.dtype) * ctx.dvol) * v, None
+        return (gE * ctx.dvol) * v, None      # (a FP64 scalar tensor: the product keeps v's type)
