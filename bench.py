@@ -89,7 +89,8 @@ def measured_traffic(kernel, lds_budget_z):
     rec = json.loads(m.group(1))
     h = hashlib.sha256()
     src = os.path.join(ROOT, "paper_0812_0244_amd", "csrc")
-    for f in ("common.hpp", "fft_lds.hpp", "fft_fast.hpp", "tile_io.hpp", "kernels.hpp", "api.hip"):
+    for f in ("common.hpp", "fft_lds.hpp", "fft_fast.hpp", "fft_split.hpp", "tile_io.hpp", "kernels.hpp",
+              "api.hip"):
         h.update(open(os.path.join(src, f), "rb").read())
     if rec.get("kernel_sources_sha256") != h.hexdigest():
         return None
@@ -576,8 +577,8 @@ def main():
             "total_points": total,
             "precision": "theta/u FFTs, contraction and divergence chain FP32; grad n chain and "
                          "reductions FP64",
-            "launch": "one HIP graph per call (%d passes, the energy reduction included, x FFT length "
-                      "classes), tile LDS budgets tuned at setup" % len(passes),
+            "launch": "one HIP graph per call (%d passes, the energy reduction included, x groups of "
+                      "grids by FFT radix class), tile LDS budgets tuned at setup" % len(passes),
             "lds_budgets": tiling,
             "radix_orders": radix,
             "radix_passes": {str(n): [radix_order(n, radix[g]) for g in ("x", "y20", "z")]

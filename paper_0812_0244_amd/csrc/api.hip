@@ -242,8 +242,8 @@ struct vdwnl_ctx {
         int threads = 0;      // per workgroup
         int len = 0;          // (axis-3 passes) the length, where it has a compile-time kernel
     };
-    // per pass: one launch per group of grids (grids whose three axes fall in
-    // the same FFT length classes); the groups' chains of passes are
+    // per pass: one launch per group of grids (grids whose three axes split
+    // into radices of the same classes); the groups' chains of passes are
     // independent of each other
     std::vector<Launch> launches[KIND_COUNT];
     int ngroups = 0;

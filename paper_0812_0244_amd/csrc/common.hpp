@@ -12,7 +12,7 @@ constexpr int kNPair = kNQ * (kNQ + 1) / 2;      // distinct phi_ab (a <= b) per
 constexpr int kTabRow = kNQ * kNQ;               // shell table entries per shell (full matrix)
 constexpr int kTabPacked = kNQ * (kNQ + 1) / 2;  // the same, packed upper triangle (some general-cell tables)
 constexpr size_t kFullRowCacheBytes = (size_t)256 << 20;   // a general-cell table this small keeps full rows
-constexpr int kThreads = 256;                    // threads per workgroup, every kernel
+constexpr int kThreads = 256;                    // threads per workgroup, the kernels with fixed strides
 constexpr int kTileCap = 4096;                   // complex elements of one LDS FFT tile
 constexpr int kLdsCap = 65536;                   // bytes of LDS one workgroup may take
 constexpr int kDenseMax = 32;                    // longest edge of grids whose divergence is a direct sum
@@ -28,8 +28,9 @@ constexpr int kMaxMc = 64;                       // largest m_c of Eq. (Sat)
 constexpr int kMaxFd = 4;                        // largest finite-difference half-width
 constexpr int kMaxN1 = 204;                      // (fused axis-1 pass; its lengths split into radices to 25)
 
-// One 1-D FFT length: radix sequence (each 2, 3, 4, 5 or 8) and the offset of
-// its twiddles W_n^k = exp(-2 pi i k / n), k < n, in the twiddle table.
+// One 1-D FFT length: its split into two radices, the radix sequence of the
+// run-time passes for lengths without one (each 2, 3, 4, 5 or 8), and the
+// offset of its twiddles W_n^k = exp(-2 pi i k / n), k < n, in the table.
 struct FftPlan {
     int n;
     int nstage;
@@ -147,8 +148,8 @@ enum ProbeKind { PROBE_THETA = 0, PROBE_THETA_K = 1, PROBE_U_K = 2, PROBE_U = 3 
 // the probes as launch kinds of their families
 enum ProbeLaunch { KP_THETA = KIND_COUNT + 1, KP_THETA_K, KP_U_K, KP_U };
 
-hipError_t launch_kind(int kind, int len_class, int precision, const LaunchArgs &a);
-hipError_t launch_probe(int probe, int len_class, int precision, const LaunchArgs &a, void *dst, int target);
+hipError_t launch_kind(int kind, int cls, int precision, const LaunchArgs &a);
+hipError_t launch_probe(int probe, int cls, int precision, const LaunchArgs &a, void *dst, int target);
 // family launchers (kernels_f32_x.hip ...) by split class: axis-3 passes (x),
 // axis-2 passes and the one-axis derivatives (y), the fused axis-1 pass (z)
 hipError_t launch_x_f32(int kind, int cls, const LaunchArgs &a);

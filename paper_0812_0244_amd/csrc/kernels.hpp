@@ -3,8 +3,11 @@
 // family (compiled in parallel).  One evaluation of E_c^nl and v_nl is eleven
 // passes over the grid with the spectral gradient (its gradient and
 // divergence one pass per grid axis each), seven with finite differences;
-// each pass is one launch per FFT length class that covers every grid of the
-// batch (a workgroup reads its work item from a tile list).
+// each pass is one launch per group of grids (by the classes their axis lengths
+// split into, fft_split.hpp, and the kind of cell) that covers every grid of
+// the group (a workgroup reads its work item from a tile list); gradient
+// directions that do not wait for each other share one launch, and the energies
+// are summed by the first workgroups of the inverse axis-2 pass.
 //
 // The 20 theta / u fields (the bulk of the traffic), the local chain and the
 // divergence of w are computed in the working precision T (float or double).
