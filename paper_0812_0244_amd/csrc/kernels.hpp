@@ -1216,6 +1216,18 @@ __global__ void __launch_bounds__(kThreads) k_y_any(const InstDev *insts, const 
 // as full rows or packed upper triangles, on the vector ALU.
 enum Contraction { CT_VEC = 0, CT_MFMA = 1, CT_GEN = 2, CT_GEN_PACKED = 3 };
 
+// Waves per SIMD the fused pass is compiled for: what the LDS of its common
+// tiles lets stand on a CU.  With packed rows the 20 offsets per lane do not
+// fit the 128 registers of four waves beside a DFT of 16: 16 values went to
+// scratch, and a lone triclinic FP32 grid's pass took 421 us at 128^3 and 522 at
+// 160 x 128 x 128 instead of 396 and 499 with three.
+template <typename T, int CT, int RMAX>
+constexpr int zmain_waves() {
+    if (sizeof(T) == 8) return 1;
+    if (RMAX <= 16) return CT == CT_GEN_PACKED && RMAX > 10 ? 3 : 4;
+    return RMAX <= 20 ? 3 : 2;
+}
+
 // Forward axis-1 FFT of the 20 theta spectra, u_a(G) = sum_b phi_ab(|G|) c_b(G)
 // with c = Theta / N (Eq. Eoffk, Eq. epsofk), the energy sum
 // sum_G w_G sum_a Re(c_a^* u_a), inverse axis-1 FFT.
@@ -1248,7 +1260,7 @@ enum Contraction { CT_VEC = 0, CT_MFMA = 1, CT_GEN = 2, CT_GEN_PACKED = 3 };
 // forward spectra c = FFT(theta)/N back in place of the tile (no contraction,
 // no inverse); 2 writes u = phi c (no inverse); 0 is the evaluation.
 template <typename T, int CT, int RMAX>
-__global__ void __launch_bounds__(kMaxThreads, sizeof(T) == 4 ? (RMAX <= 16 ? 4 : RMAX <= 20 ? 3 : 2) : 1)
+__global__ void __launch_bounds__(kMaxThreads, (zmain_waves<T, CT, RMAX>()))
 k_z_main(const InstDev *insts, const Tile *tiles, const int2 *cols, const void *twv, int probe) {
     extern __shared__ __align__(16) unsigned char smem[];
     using Ch = Chunk<T>;
