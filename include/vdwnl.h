@@ -149,7 +149,7 @@ int vdwnl_energy_potential(vdwnl_ctx *ctx, const void *n_dev, void *v_dev, doubl
  * and calls no allocating library routine.  Every device structure of the
  * evaluation (the per-grid fields and spectra, tile lists, twiddles, kernel
  * rows, partial sums, instance table and energies) lives in one buffer of
- * 64 MiB, a static device array of the library, one per GPU the library runs
+ * 65 MiB, a static device array of the library, one per GPU the library runs
  * on (each held from the library's first use of that GPU until the process
  * ends; its address is taken when a context is created).  A plan fits when
  * its whole image does: about 64^3 points in FP32 or 48^3 in FP64 for cubic

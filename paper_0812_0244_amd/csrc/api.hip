@@ -1589,7 +1589,10 @@ static int probe_stage(vdwnl_ctx *c, int stage, int target, void *dst, hipStream
 // address, from the library's first use of the device until the process
 // ends).  Host code never uses the array's name as an address: the pointer
 // comes from hipGetSymbolAddress, once per device, with that device current.
-constexpr size_t kScratchBytes = (size_t)64 << 20;
+// 65 MiB: 64 for what the plans took with wider tiles, and room for the longer
+// tile lists of the present ones (up to 0.7% of an image, on grids with a short
+// axis 1), so that every plan that fitted then still does.
+constexpr size_t kScratchBytes = (size_t)65 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
