@@ -298,10 +298,11 @@ int vdwnl_set_graph(vdwnl_ctx *ctx, int32_t on);
  * clocks have risen before any timing, keeps per pass group the budget (for
  * the fused axis-1 pass, the budget and unit) with the least time over the
  * group's passes, plans with the choices and remembers them, keyed by the
- * device architecture, its LDS size,
- * the precision, the gradient mode and the exact grid list: for the rest of
+ * device architecture, its LDS size, the kernels' schedule (entries tuned for
+ * other tiles are not taken), the precision, the gradient mode and the exact
+ * grid list: for the rest of
  * the process, and in the tuning file for later processes.  The file is a
- * JSON object with one entry per line, "<arch>/<key hash>": [five budgets,
+ * JSON object with one entry per line, "<arch>/...<key hash>": [five budgets,
  * the contraction unit, five radix orders],
  * at $VDWNL_TUNE_CACHE (an empty value: no file), else
  * $XDG_CACHE_HOME/vdwnl/tuning.json or $HOME/.cache/vdwnl/tuning.json; a file

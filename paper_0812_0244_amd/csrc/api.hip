@@ -568,10 +568,11 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
 }
 
 // Tuned LDS budgets, keyed by the device architecture, LDS size, precision,
-// gradient mode and the exact list of grid shapes and cells: a map for the
+// gradient mode, the kernels' schedule and the exact list of grid shapes and
+// cells: a map for the
 // process, backed by a file so that later processes reuse them.  The file is
 // a JSON object with one entry per line,
-//   "<arch>/<hash of the rest of the key>": [x, y20, yaux, z, zaux, contraction,
+//   "<arch>/.../<hash of the rest of the key>": [x, y20, yaux, z, zaux, contraction,
 //                                              five radix orders in the same group order],
 // at $VDWNL_TUNE_CACHE (empty: no file), else $XDG_CACHE_HOME/vdwnl/tuning.json
 // or $HOME/.cache/vdwnl/tuning.json.  A file that cannot be read or written
@@ -579,6 +580,11 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
 static std::mutex g_tuned_mu;
 static std::map<std::string, std::vector<size_t>> g_tuned;
 constexpr int kTuneVals = 2 * TG_COUNT + 1;   // the five budgets, the contraction unit, five radix orders
+// What a budget means to the kernels, raised when their tiles change: an entry
+// timed on other tiles is not this plan's (a z budget of 16 KB, tuned for tiles
+// of up to 16 columns, would hold 96^3 FP32 to single ones: 302 us an evaluation
+// against 293).  Entries without the number are of the tiles before 2.
+constexpr int kTuneSchedule = 2;
 
 static std::string plan_key(const vdwnl_ctx *c) {
     std::string k = std::to_string(c->precision) + "/" + std::to_string(c->grad_mode) + "/" + std::to_string(c->lds_cap);
@@ -594,8 +600,8 @@ static std::string plan_key(const vdwnl_ctx *c) {
     // FNV-1a of the whole key, behind the readable part
     uint64_t h = 1469598103934665603ull;
     for (unsigned char ch : k) { h ^= ch; h *= 1099511628211ull; }
-    std::snprintf(buf, sizeof(buf), "%s/p%d/g%d/l%zu/n%zu/%016llx", c->arch.c_str(), c->precision, c->grad_mode,
-                  c->lds_cap, c->grids.size(), (unsigned long long)h);
+    std::snprintf(buf, sizeof(buf), "%s/s%d/p%d/g%d/l%zu/n%zu/%016llx", c->arch.c_str(), kTuneSchedule, c->precision,
+                  c->grad_mode, c->lds_cap, c->grids.size(), (unsigned long long)h);
     return buf;
 }
 
