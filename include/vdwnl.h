@@ -81,7 +81,7 @@ const char *vdwnl_last_error(const vdwnl_ctx *ctx);
  * which later contexts take blocks before they allocate, and the pool is
  * held until the process ends); later evaluations allocate nothing.  Tile
  * shapes follow one LDS budget per
- * pass group: a budget set tuned by vdwnl_autotune for the same grid list,
+ * pass group where they have a choice (vdwnl_set_tiling): a budget set tuned by vdwnl_autotune for the same grid list,
  * precision, gradient mode and device architecture is reused (from this
  * process, or from the tuning file of an earlier one; see vdwnl_autotune),
  * else 64 KB each. */
@@ -292,12 +292,14 @@ int vdwnl_set_graph(vdwnl_ctx *ctx, int32_t on);
 
 /* Schedule tuning for the planned grids: evaluates the batch (n_ptrs[nb],
  * v_ptrs[nb] as for vdwnl_energy_potential_batched; v is overwritten) once
- * plus `reps` timed times (1..100) for each candidate LDS budget (and, for
+ * plus `reps` timed times (1..100) for each candidate LDS budget that gives
+ * some pass group other tiles (and, for
  * FP32 orthorhombic grids, each contraction unit), the first
  * candidate after some 300 ms of untimed evaluations so that the device's
  * clocks have risen before any timing, keeps per pass group the budget (for
  * the fused axis-1 pass, the budget and unit) with the least time over the
- * group's passes, plans with the choices and remembers them, keyed by the
+ * group's passes (64 KB for a group whose tiles are the same under every
+ * budget, see vdwnl_set_tiling), plans with the choices and remembers them, keyed by the
  * device architecture, its LDS size, the kernels' schedule (entries tuned for
  * other tiles are not taken), the precision, the gradient mode and the exact
  * grid list: for the rest of
@@ -364,7 +366,11 @@ int vdwnl_get_tiling(const vdwnl_ctx *ctx, int32_t max_groups, int64_t *lds_budg
 
 /* Set the five LDS budgets (bytes, same order, each in [4096, the device's
  * LDS per workgroup]) and re-plan the tiles of the planned grids (the
- * workspace is rebuilt at the next evaluation). */
+ * workspace is rebuilt at the next evaluation).  A budget acts where its group
+ * has a choice: the rows of an axis-3 tile, one column or two per tile with the
+ * contraction, and the tile widths of axis-2 lengths that do not split into two
+ * radices (above 405).  The other tiles follow from the lengths, whatever the
+ * budget. */
 int vdwnl_set_tiling(vdwnl_ctx *ctx, int32_t ngroups, const int64_t *lds_budget);
 
 /* Build the kernel table that vdwnl_set_kernel_table takes, on GPU `device`

@@ -567,6 +567,23 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     g.wdy = dwidth(N2, c->pref[TG_YAUX]);
 }
 
+// The tile sizes that the group's LDS budget decides, over the grids: none where
+// the tiles follow from the length's split.
+static std::vector<int> tile_sizes(const vdwnl_ctx *c, int group) {
+    std::vector<int> out;
+    for (const Grid &g : c->grids) {
+        const bool any2 = y_class(c, g) == kLenGeneric;
+        switch (group) {
+            case TG_X: out.push_back(g.bmain); break;
+            case TG_Y20: out.push_back(any2 ? g.wy20 : 0); break;
+            case TG_YAUX: out.push_back(any2 && c->grad_mode == 0 ? g.wdy : 0); break;
+            case TG_Z: out.push_back(g.k3main); break;
+            default: break;
+        }
+    }
+    return out;
+}
+
 // Tuned LDS budgets, keyed by the device architecture, LDS size, precision,
 // gradient mode, the kernels' schedule and the exact list of grid shapes and
 // cells: a map for the
@@ -1999,11 +2016,28 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
     if (!ctx) return VDWNL_E_ARG;
     if (!ctx->have_grid || !ctx->have_table) return fail(ctx, VDWNL_E_STATE, "grid and kernel table must both be set");
     if (reps < 1 || reps > 100) return fail(ctx, VDWNL_E_ARG, "reps must be in 1..100");
-    // candidate budgets; the tile sizing keeps at least one unit per tile, so
-    // a budget below some pass's minimum simply gives that pass its minimum
-    std::vector<size_t> cand;
+    // candidate budgets, the default first; the tile sizing keeps at least one
+    // unit per tile, so a budget below some pass's minimum simply gives that
+    // pass its minimum
+    std::vector<size_t> cand = {std::min<size_t>(ctx->lds_cap, kLdsCap)};
     for (size_t b : {16384, 24576, 32768, 49152, 65536, 98304, 131072})
-        if (b <= ctx->lds_cap) cand.push_back(b);
+        if (b <= ctx->lds_cap && b != cand[0]) cand.push_back(b);
+    // plan[ci][gi]: the first candidate that gives group gi the tiles candidate
+    // ci does.  Each plan is timed once, so that noise between candidates that
+    // plan the same launches chooses nothing (axis-2 lengths that split and the
+    // axis-1 derivatives have one plan).
+    std::vector<std::vector<size_t>> plan(cand.size(), std::vector<size_t>(TG_COUNT, 0));
+    {
+        std::vector<std::vector<std::vector<int>>> sizes(cand.size());
+        for (size_t ci = 0; ci < cand.size(); ++ci) {
+            for (auto &p : ctx->pref) p = cand[ci];
+            for (auto &g : ctx->grids) size_tiles(ctx, g);
+            for (int gi = 0; gi < TG_COUNT; ++gi) {
+                sizes[ci].push_back(tile_sizes(ctx, gi));
+                while (sizes[plan[ci][gi]][gi] != sizes[ci][gi]) ++plan[ci][gi];
+            }
+        }
+    }
     const bool timing0 = ctx->timing;
     ctx->img_valid = ctx->img_built = false;     // (the candidates' tiles differ from the image's)
     for (auto &x : ctx->variant) x = 0;
@@ -2020,6 +2054,9 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
     std::vector<double> E((size_t)nb * 2);
     for (size_t ui = 0; ui < units.size() && rc == VDWNL_OK; ++ui)
         for (size_t ci = 0; ci < cand.size() && rc == VDWNL_OK; ++ci) {
+            bool fresh = false;
+            for (int gi = 0; gi < TG_COUNT; ++gi) fresh = fresh || ((ui == 0 || gi == TG_Z) && plan[ci][gi] == ci);
+            if (!fresh) continue;
             ctx->contraction = units[ui];
             for (auto &p : ctx->pref) p = cand[ci];
             for (auto &g : ctx->grids) size_tiles(ctx, g);
@@ -2039,8 +2076,9 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
             for (int k = 0; k < KIND_COUNT; ++k) t[ui][ci][k] = ctx->pass_ms[k];
         }
     // per group, the budget with the least time over the group's passes (a
-    // group with no pass in this gradient mode keeps the default); for the
-    // fused axis-1 group, the budget and the contraction unit together
+    // group with one plan, or no pass in this gradient mode, keeps the
+    // default); for the fused axis-1 group, the budget and the contraction unit
+    // together
     const std::vector<std::vector<int>> groups = {{KX_THETA, KX_ASSEMBLE},
                                                   {KY_20F, KY_20I},
                                                   {KG_Y, KD_Y},
@@ -2050,9 +2088,10 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
     int best_unit = VDWNL_CONTRACTION_VECTOR;
     for (int gi = 0; gi < TG_COUNT; ++gi) {
         double bt = 1e300;
-        best[gi] = std::min<size_t>(ctx->lds_cap, kLdsCap);
+        best[gi] = cand[0];
         for (size_t ui = 0; ui < (gi == TG_Z ? units.size() : 1); ++ui)
             for (size_t ci = 0; rc == VDWNL_OK && ci < cand.size(); ++ci) {
+                if (plan[ci][gi] != ci) continue;
                 double sum = 0.0;
                 for (int k : groups[gi]) sum += t[ui][ci][k];
                 if (sum > 0.0 && sum < bt) {
