@@ -328,17 +328,15 @@ int vdwnl_autotune(vdwnl_ctx *ctx, int32_t nb, const void *const *n_ptrs, void *
  *     transform runs as its length's most even split into two radices.
  * vdwnl_autotune chooses the contraction unit together with the LDS budgets
  * (and a plan reuses tuned choices as it does the budgets); untuned, the
- * matrix cores and order 0.  Setting a choice
+ * matrix cores and order 0.  Setting the contraction unit
  * re-plans the launches (the workspace is rebuilt at the next evaluation).
  * VDWNL_E_ARG for an unknown choice or value; VDWNL_E_STATE without a planned
  * grid. */
 enum {
     VDWNL_SCHEDULE_CONTRACTION = 0,
-    /* radix order of the transforms of each pass group (0..5): every axis-3
+    /* a radix order (0..5) for each pass group: every axis-3
      * transform, the axis-2 transforms of the 20 spectra, the other axis-2
-     * transforms, the fused axis-1 pass, the other axis-1 passes.  Each length
-     * with a compile-time plan has one to six orders (vdwnl_radix_order),
-     * and a larger value takes its last; other lengths have one. */
+     * transforms, the fused axis-1 pass, the other axis-1 passes */
     VDWNL_SCHEDULE_RADIX_X = 1,
     VDWNL_SCHEDULE_RADIX_Y20 = 2,
     VDWNL_SCHEDULE_RADIX_YAUX = 3,
@@ -349,9 +347,10 @@ enum { VDWNL_CONTRACTION_VECTOR = 0, VDWNL_CONTRACTION_MATRIX = 1 };
 int vdwnl_set_schedule(vdwnl_ctx *ctx, int32_t what, int32_t value);
 int vdwnl_get_schedule(const vdwnl_ctx *ctx, int32_t what, int32_t *value);
 
-/* The radices (each 2, 3, 4, 5, 8 or 16, in order) that make up length n in
- * radix order `order` (0..5; a larger order than the length has
- * takes its last): up to max_radices values into radices[] (host array).
+/* A factorisation of length n: the radices (each 2, 3, 4, 5, 8 or 16, in order)
+ * that make it up in radix order `order` (0..5; a larger order than the length
+ * has takes its last).  What VDWNL_SCHEDULE_RADIX_* names; the transforms run as
+ * two radices whatever the order.  Up to max_radices values into radices[] (host array).
  * Returns their number, VDWNL_E_ARG for bad arguments, or
  * VDWNL_E_UNSUPPORTED_SIZE for a length with a prime factor above 5.  Host
  * only (no context, no device). */

@@ -2137,8 +2137,11 @@ int vdwnl_set_schedule(vdwnl_ctx *ctx, int32_t what, int32_t value) {
         return fail(ctx, VDWNL_E_ARG, "unknown schedule choice");
     }
     if (!ctx->have_grid) return fail(ctx, VDWNL_E_STATE, "no grid planned");
-    if (what == VDWNL_SCHEDULE_CONTRACTION) ctx->contraction = value;
-    else ctx->variant[what - VDWNL_SCHEDULE_RADIX_X] = value;
+    if (what != VDWNL_SCHEDULE_CONTRACTION) {
+        ctx->variant[what - VDWNL_SCHEDULE_RADIX_X] = value;   // (kept and reported; no launch depends on it)
+        return VDWNL_OK;
+    }
+    ctx->contraction = value;
     free_device(ctx);
     refresh_image(ctx);
     return VDWNL_OK;
