@@ -29,6 +29,18 @@ PEAK_HBM_GBS = 8000.0
 ALG_BYTES_PER_POINT = {32: (4 * 20 + 28) * 4, 64: (4 * 20 + 28) * 8}
 
 
+DENSE_EDGE = 32     # grids with no longer edge take the divergence as direct sums in x_div
+
+
+def own_launches(passes, general=False):
+    """The passes that launch kernels of their own: the energy sums run inside
+    y_20i, and the gradient's directions that do not wait for each other inside
+    x_deriv (all three in orthorhombic cells, axes 3 and 2 in general ones).  The
+    gaps that events leave around the others are no kernel's time."""
+    merged = ("reduce", "y_deriv") if general else ("reduce", "y_deriv", "z_deriv")
+    return {k: v for k, v in passes.items() if k not in merged}
+
+
 def pass_bytes(name, shapes, s):
     """Algorithmic bytes one launch of a pass moves over all grids: what it
     must read and write given its inputs and outputs (spectra as N1 N2
@@ -39,17 +51,19 @@ def pass_bytes(name, shapes, s):
         N = n1 * n2 * n3
         NH = n1 * n2 * (n3 // 2 + 1)
         c = 2 * s
+        dense = max(n1, n2, n3) <= DENSE_EDGE
         b = {
-            # spectral gradient and divergence, one pass per axis
-            "x_deriv": 2 * N * s, "y_deriv": 2 * N * s, "z_deriv": 2 * N * s,
-            "x_div": 3 * N * s, "y_div": 3 * N * s, "z_div": 3 * N * s,
+            # spectral gradient (three directions) and divergence (one pass per
+            # axis, or one in all)
+            "x_deriv": 6 * N * s,
+            "x_div": (5 if dense else 3) * N * s, "y_div": 0 if dense else 3 * N * s,
+            "z_div": 0 if dense else 3 * N * s,
             "x_theta": 4 * N * s + 20 * NH * c,
             "y_20f": 40 * NH * c, "z_main": 40 * NH * c, "y_20i": 40 * NH * c,
             "x_assemble": 20 * NH * c + 8 * N * s,
             # finite-difference gradient mode
             "fd_grad": 4 * N * s,
             "fd_div": 5 * N * s,
-            "reduce": 0,
         }[name]
         tot += b
     return tot
@@ -187,9 +201,9 @@ def single_leg(name, wl, table, steps, warmup, log):
             for _ in range(steps):
                 lib.energy_potential(nt.data_ptr(), vt.data_ptr(), stream)
             torch.cuda.synchronize()
-            passes = lib.pass_times()
+            passes = own_launches(lib.pass_times())
             lib.set_timing(False)
-            dom = max((k for k in passes if k != "reduce"), key=lambda k: passes[k][0])
+            dom = max(passes, key=lambda k: passes[k][0])
             dom_ms = passes[dom][0] / max(passes[dom][1], 1)
             r["passes_ms_per_step"] = {k: v[0] / max(v[1], 1) for k, v in passes.items()}
             r["dominant"] = {"kernel": dom, "ms": dom_ms, "algorithmic_bytes": pass_bytes(dom, [wl.shape], 4),
@@ -237,7 +251,7 @@ def main():
     ap.add_argument("--lds-budgets", type=str, default=None,
                     help="x,y20,yaux,z,zaux LDS budgets in bytes (fixes the tiles; no tuning)")
     ap.add_argument("--radix-orders", type=str, default=None,
-                    help="x,y20,yaux,z,zaux radix orders 0..5 (with --lds-budgets; no tuning)")
+                    help="accepted and ignored: every transform runs as its length's split into two radices")
     ap.add_argument("--contraction", type=int, default=None,
                     help="0: vector ALU, 1: matrix cores (with --lds-budgets; no tuning)")
     ap.add_argument("--fd-mode", type=int, default=3,
@@ -260,7 +274,7 @@ def main():
     import torch
 
     import workloads as W
-    from paper_0812_0244_amd.binding import VdwNl, build_kernel_table, radix_order
+    from paper_0812_0244_amd.binding import VdwNl, build_kernel_table
 
     def log(msg):
         print("[bench] " + msg, file=sys.stderr, flush=True)
@@ -297,16 +311,12 @@ def main():
     t0 = time.time()
     if args.lds_budgets:
         lib.set_tiling([int(x) for x in args.lds_budgets.split(",")])
-        if args.radix_orders:
-            lib.set_radix_orders([int(x) for x in args.radix_orders.split(",")])
         if args.contraction is not None:
             lib.set_contraction(args.contraction)
     elif not args.no_autotune:
         lib.autotune(nptr, vptr, reps=5, stream=stream)
     tiling = lib.get_tiling()
-    radix = lib.get_radix_orders()
-    log("tile budgets %s, contraction unit %d, radix orders %s (%.1f s)"
-        % (tiling, lib.get_contraction(), radix, time.time() - t0))
+    log("tile budgets %s, contraction unit %d (%.1f s)" % (tiling, lib.get_contraction(), time.time() - t0))
     for _ in range(args.warmup):
         lib.energy_potential_batched(nptr, vptr, stream)
     torch.cuda.synchronize()
@@ -327,7 +337,7 @@ def main():
     for _ in range(args.steps):
         lib.energy_potential_batched(nptr, vptr, stream)
     torch.cuda.synchronize()
-    passes = lib.pass_times()
+    passes = own_launches(lib.pass_times())
     lib.set_timing(False)
     ev_ms = sum(v[0] for v in passes.values()) / args.steps
     log("fp32 batched (event-timed launches): %.3f ms/step of passes" % ev_ms)
@@ -365,7 +375,7 @@ def main():
 
     # dominant pass and its roofline (bytes and time per step: the pass's
     # launches over every grid of the batch)
-    dom = max((k for k in passes if k != "reduce"), key=lambda k: passes[k][0])
+    dom = max(passes, key=lambda k: passes[k][0])
     dom_ms = passes[dom][0] / max(passes[dom][1], 1)
     dom_bytes = pass_bytes(dom, shapes, 4)
     achieved = dom_bytes / (dom_ms * 1e-3) / 1e9
@@ -401,7 +411,7 @@ def main():
               "E_sum": float(Exc.sum()), "E_x_sum": float(sl[:, 0].sum()), "E_c_lda_sum": float(sl[:, 1].sum())}
 
     # ---- the same workload with the finite-difference gradient (the paper's
-    # own choice; seven passes instead of eleven), FP32 batched
+    # own choice; one gradient and one divergence pass), FP32 batched
     del lib
     fd = None
     if args.fd_mode > 0:
@@ -430,7 +440,7 @@ def main():
         for _ in range(args.steps):
             lib.energy_potential_batched(nptr, vfptr, stream)
         torch.cuda.synchronize()
-        fd_passes = lib.pass_times()
+        fd_passes = own_launches(lib.pass_times())
         lib.set_timing(False)
         del lib
         log("fp32 batched, finite differences m=%d (graph replay): %.3f ms/step, median %.3f"
@@ -476,7 +486,7 @@ def main():
         for _ in range(args.steps):
             lib.energy_potential_batched(nptr, vtptr, stream)
         torch.cuda.synchronize()
-        tr_passes = lib.pass_times()
+        tr_passes = own_launches(lib.pass_times(), general=True)
         lib.set_timing(False)
         _, ws_bytes = lib.info()
         del lib
@@ -577,12 +587,9 @@ def main():
             "total_points": total,
             "precision": "theta/u FFTs, contraction and divergence chain FP32; grad n chain and "
                          "reductions FP64",
-            "launch": "one HIP graph per call (%d passes, the energy reduction included, x groups of "
-                      "grids by FFT radix class), tile LDS budgets tuned at setup" % len(passes),
+            "launch": "one HIP graph per call (up to %d launches, the energy sums in one of them, per group of "
+                      "grids of one radix class), tile LDS budgets tuned at setup" % len(passes),
             "lds_budgets": tiling,
-            "radix_orders": radix,
-            "radix_passes": {str(n): [radix_order(n, radix[g]) for g in ("x", "y20", "z")]
-                             for n in sorted({s[0] for s in shapes})},
         },
         "fp64_plain": {"ms_per_step": ms64, "value": total / (ms64 * 1e-3),
                        "max_rel_E_fp32_batched_vs_fp64_plain": max_rel,
