@@ -618,7 +618,7 @@ def main():
                      "passes_design_bytes_per_step": path_bytes,
                      "passes_design_bytes_per_point": path_bytes / total},
         # the same pass against the vector-ALU roofline (its counters show it
-        # bound by instruction issue, not bandwidth)
+        # bound by neither: latency at three workgroups per CU)
         "roofline_valu": None if dom != "z_main" else {
             "bound": "alu", "kernel": dom, "unit": "TFLOP/s",
             "achieved": z_main_flops(shapes) / (dom_ms * 1e-3) / 1e12, "peak": PEAK_FP32_VALU_TFS,

@@ -408,8 +408,12 @@ static size_t xpass_lds(const Grid &g, size_t b, size_t rs) {
 
 // Rows of an axis-3 tile and its threads: a point each, in whole waves with
 // few idle lanes among 128 to 256 threads: the most threads (128^3 and 64^3 in
-// FP32, theta pass of batches: 222 and 112 us with 256, 235 and 120 with 128),
-// or the fewest while the grid gives a CU less than two tiles; longer rows
+// FP32: 399 against 405 us an evaluation with the fewest, sixteen 64^3 803
+// against 819; 128^3 in FP64 923 against 949), or the fewest while the grid
+// gives a CU less than two tiles (there either choice is within 1%, 24^3 to
+// 60^3).  One more row is taken while it idles at most 3% more of the lanes, on
+// the small grids only if it idles 4% fewer: with any gain taken instead, 64^3 in
+// FP64 172 -> 173 us and 128^3 in FP32 399 -> 405, the rest equal; longer rows
 // stand alone.
 static int xpass_rows(const Grid &g, size_t rs, size_t budget) {
     const int n3 = g.s[2], rows = g.s[0] * g.s[1];
@@ -519,10 +523,11 @@ static int zmain_threads(const Grid &g, int K, size_t cs) {
 // The divergence (and the gradient in general cells, which otherwise takes
 // two launches) as direct sums over each axis, one launch, instead of
 // transforms, whose three passes each update the potential: edges to
-// kDenseMax.  24^3 in FP64 83 -> 75 us per evaluation; at 48^3 the sums' work
-// (N terms a point and axis) already takes the launches' place (triclinic FP64
-// 154 -> 152, 24 grids of edges 24 to 48 309 -> 365 us if all took it, 309 ->
-// 302 with edges to 32).
+// kDenseMax.  Transforms against sums, us an evaluation: 24^3 in FP64 74 and 69
+// (triclinic 85 and 74), 32^3 83 and 76 (99 and 87), 24 grids of edges 24 to 32
+// in FP32 202 and 198; at 48^3 the sums' work (N terms a point and axis) already
+// takes the launches' place (triclinic FP64 154 and 152, 24 grids of edges 24 to
+// 48 309 and 365 if all took it, 300 with edges to 32).
 static bool dense_deriv(const Grid &g) { return std::max(g.s[0], std::max(g.s[1], g.s[2])) <= kDenseMax; }
 
 // Tile shapes of grid g from the LDS budget of each pass group: each tile as
@@ -533,7 +538,7 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     auto ypass = [&](size_t w, size_t c2) { return (N2 + (N2 | 1) * w) * c2; };
     // complex elements per LDS tile of the run-time radix passes (axis-2
     // lengths without a split), bounded by their per-thread register arrays
-    auto cap = [](size_t) { return (size_t)kTileCap; };
+    const size_t cap = kTileCap;
     g.bmain = xpass_rows(g, rs, c->pref[TG_X]);
     // rows of a stencil (or direct-sum derivative) tile: 256 to 4096 points, some 1024 tiles per grid where
     // it has the points (48^3 ran 28 workgroups of 4096 points, a ninth of the
@@ -544,13 +549,15 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     }
     // fused axis-1 tiles: two columns (a pair k2, N2 - k2 shares its kernel
     // rows) where they fit the budget; in FP64, whose columns are twice as
-    // large, only up to 16 KB: a second workgroup per CU is worth more than the
-    // shared rows (one column against two, us per evaluation: 96^3 FP64 469
-    // and 494, 45 x 50 x 75 168 and 176, 48^3 triclinic 177 and 186, 24^3 109
-    // and 107; in FP32 96^3 302 and 293, 160 x 160 x 320 2274 and 2160)
+    // large, only up to 16 KB: the tile of two at long axes leaves too few
+    // workgroups per CU (one column against two, us per evaluation: 128^3 FP64
+    // 922 and 1010, 48^3 triclinic 140 and 144, 27 x 30 x 27 77 and 79; nothing
+    // in it from 16^3 to 25^3, the lengths under the limit, and at 96^3, 376 and
+    // 376; 45 x 50 x 75 148 and 146.  In FP32 64^3 117 and 111, 96^3 222 and 211,
+    // 160 x 160 x 320 1895 and 1747)
     g.k3main = zmain_lds(g, 2, cs) <= std::min(c->pref[TG_Z], cs == 8 ? c->pref[TG_Z] : (size_t)16384) ? 2 : 1;
     g.wy20 = 1;
-    while ((size_t)(g.wy20 + 1) * N2 <= cap(N2) && ypass(g.wy20 + 1, cs) <= c->pref[TG_Y20]) ++g.wy20;
+    while ((size_t)(g.wy20 + 1) * N2 <= cap && ypass(g.wy20 + 1, cs) <= c->pref[TG_Y20]) ++g.wy20;
     if (g.wy20 > 1) g.wy20 &= ~1;   // even widths: 16-byte aligned FP32 rows
     // derivative tiles along an axis 2 with run-time radices: i3 columns in
     // pairs (one FP64 line each), within the group's budget
@@ -558,7 +565,7 @@ static void size_tiles(const vdwnl_ctx *c, Grid &g) {
     // so that the runs of i3 start and end on 128-byte boundaries)
     auto dwidth = [&](size_t L, size_t budget) {
         int w = 2;
-        while ((size_t)(w + 2) <= N3 && (size_t)(w / 2 + 1) * L <= cap(L) && deriv_lds(L, w / 2 + 1, 16) <= budget)
+        while ((size_t)(w + 2) <= N3 && (size_t)(w / 2 + 1) * L <= cap && deriv_lds(L, w / 2 + 1, 16) <= budget)
             w += 2;
         w = std::min<int>(w, (int)N3);
         if (w < (int)N3 && w >= 32) w &= ~31;
@@ -599,8 +606,8 @@ static std::map<std::string, std::vector<size_t>> g_tuned;
 constexpr int kTuneVals = 2 * TG_COUNT + 1;   // the five budgets, the contraction unit, five radix orders
 // What a budget means to the kernels, raised when their tiles change: an entry
 // timed on other tiles is not this plan's (a z budget of 16 KB, tuned for tiles
-// of up to 16 columns, would hold 96^3 FP32 to single ones: 302 us an evaluation
-// against 293).  Entries without the number are of the tiles before 2.
+// of up to 16 columns, would hold 96^3 FP32 to single ones: 222 us an evaluation
+// against 211).  Entries without the number are of the tiles before 2.
 constexpr int kTuneSchedule = 2;
 
 static std::string plan_key(const vdwnl_ctx *c) {
@@ -1397,7 +1404,7 @@ static int prepare_device(vdwnl_ctx *c) {
 // energies to pinned host memory.  With timing on, events bracket each pass.
 // With chains (graph capture of a batch of several groups) each group's
 // passes go to a stream of its own, forked from st and joined back before
-// the reduction: the groups' chains are independent, so a pass of one group
+// the copy of the energies: the groups' chains are independent, so a pass of one group
 // can run beside a pass of another.  Otherwise the passes go in order on st.
 static int enqueue(vdwnl_ctx *c, const DevPtrs &P, const InstDev *hinst, double *hE, int nb, hipStream_t st,
                    bool chains = false) {
@@ -1695,8 +1702,8 @@ static void refresh_image(vdwnl_ctx *c) {
 
 // One evaluation of a single planned grid with every device structure in
 // this device's scratch: the image is copied in when the scratch holds
-// another one, then the instance table, the passes launched one by one, the
-// reduction and the energies, all on st; returns after st has finished.
+// another one, then the instance table, the passes launched one by one and the
+// energies, all on st; returns after st has finished.
 static int run_noalloc(vdwnl_ctx *c, const void *n_dev, void *v_dev, double *E_out, hipStream_t st) {
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hipfail(c, e, "hipSetDevice");

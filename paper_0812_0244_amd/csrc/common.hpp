@@ -14,15 +14,16 @@ constexpr int kTabPacked = kNQ * (kNQ + 1) / 2;  // the same, packed upper trian
 constexpr size_t kFullRowCacheBytes = (size_t)256 << 20;   // a general-cell table this small keeps full rows
 constexpr int kThreads = 256;                    // threads per workgroup, the kernels with fixed strides
 constexpr int kTileCap = 4096;                   // complex elements of one LDS FFT tile
-constexpr int kLdsCap = 65536;                   // bytes of LDS one workgroup may take
+constexpr int kLdsCap = 65536;                   // default LDS budget of a pass group (tiles whose size follows from
+                                                 // the length may take more, up to the device's)
 constexpr int kDenseMax = 32;                    // longest edge of grids whose divergence is a direct sum
 constexpr int kDenseClass = 16;                  // launch class of those derivatives
 constexpr size_t kReduceLds = 4 * 256 * sizeof(double);   // running sums of the energy reduction
 constexpr int kMaxStages = 16;
 // Most threads of a workgroup.  Five to seven waves do not spread evenly over
-// a CU's four SIMDs: the theta pass of 160 x 160 x 320 takes 317 us with 256
-// threads and 506 with 320, of four 128^3 grids 292 with 256 and 541 with 320
-// (the same tiles).
+// a CU's four SIMDs: on the same tiles the theta and assembly passes of
+// 160 x 160 x 320 take 275 and 329 us with 256 threads and 353 and 445 with 320,
+// of four 128^3 grids 237 and 266 with 256 and 248 and 362 with 320.
 constexpr int kMaxThreads = 256;
 constexpr int kMaxMc = 64;                       // largest m_c of Eq. (Sat)
 constexpr int kMaxFd = 4;                        // largest finite-difference half-width

@@ -274,6 +274,11 @@ __device__ __forceinline__ void load_consts(const Consts *cst, T *qm, T *Mm, T *
 // items on different banks.
 // Compile-time radices (CR1 CR2 = the length; 0: run-time ones) turn the
 // positions and strides of the common lengths into constants.
+// Both passes are bound by the arithmetic and latency of the local chain between
+// their loads and stores.  Against whole lines in radix passes (theta, assembly,
+// traced): 90 x 100 x 108 in FP32 87 -> 43 us and 90 -> 36, 96^3 39 -> 31 and
+// 37 -> 32, 160 x 160 x 320 331 -> 268 and 328 -> 331; at 128^3, whose lines had
+// three passes of radix 8 and 4, 61 -> 60 and 55 -> 66.
 template <typename T, int CR1, int CR2>
 struct XTile {
     static constexpr int kP = kNQ / 2;                        // pair lines per row
@@ -737,10 +742,13 @@ __global__ void __launch_bounds__(kThreads) k_fd_div(const InstDev *insts, const
 // the registers of one item, so a line crosses LDS twice.  One kernel takes
 // every axis (run-time strides), so the three independent gradient passes of
 // an orthorhombic grid are one launch.  Bound by the latency of its few
-// dependent steps on small grids, by memory on large ones (the three gradient
-// directions together 41 -> 13 us at 96^3 and 83 -> 18 at 90 x 100 x 108 in
-// FP32, 198 -> 78 at 160 x 160 x 320; the three divergence passes 43 -> 30,
-// 76 -> 33 and 143 -> 87).
+// dependent steps on small grids, by memory on large ones (against lines held
+// in LDS, traced: the three gradient directions together 41 -> 12 us at 96^3 and
+// 84 -> 16 at 90 x 100 x 108 in FP32, 193 -> 81 at 160 x 160 x 320; the three
+// divergence passes 39 -> 22, 77 -> 26 and 134 -> 80).  The FP32 gradient of the
+// two largest classes does not fit its registers: 12 bytes a lane go to scratch
+// in the class of radices to 20 and 64 in that to 27, in every direction of the
+// launch (128 x 125 x 128: 54 -> 36 us all the same).
 // tile: slot = axis (3, 2, 1); lanes = tile_lanes of the axis's R2.
 //   axis 3: a = first row (i1 N2 + i2), b = rows (even, <= 2 << lanes; rows 2p, 2p+1
 //     form line p).  MODE 0: grad[2] = W[2][2] d_3 n (orthorhombic) or d_3 n
@@ -916,8 +924,8 @@ __global__ void __launch_bounds__(kMaxThreads, 2) k_deriv(const InstDev *insts, 
 // derivative row by row.  A point then needs its neighbours only, so all three
 // axes are one launch: the gradient in any cell, and v = v_loc - sum_c d_c q_c,
 // whose three passes each update v.  Small grids are bound by the number of
-// dependent launches, not by these sums (24^3 in FP64: one pass of 9 us for
-// three of 7, event-timed, 83 -> 75 us per evaluation).
+// dependent launches, not by these sums (24^3 in FP64: one pass of 10 us for
+// three of 7, event-timed, 74 -> 69 us per evaluation).
 // tile: a = first row (i1 N2 + i2), b = rows.
 template <typename T, typename C>
 __device__ __forceinline__ C dense_sum(gptr<const T> f, int i, int n, int st, const C *w) {
@@ -1066,7 +1074,7 @@ __global__ void __launch_bounds__(kThreads) k_deriv_any(const InstDev *insts, co
 // the summation order is the grid's own), eight loads in flight each.  These
 // are the first workgroups of the inverse axis-2 pass, beside its tiles: as a
 // launch of its own at the end, one workgroup a grid with one load in flight
-// per lane, the reduction took 4 us on 24^3, 25 us on 128^3 and 69 us on
+// per lane, the reduction took 3 us on 24^3, 18 us on 128^3 and 70 us on
 // 160 x 160 x 320.
 __device__ __forceinline__ void reduce_energies(const InstDev &I, double *acc) {
     constexpr int V = 256, U = 8;
@@ -1109,9 +1117,8 @@ __device__ __forceinline__ void reduce_energies(const InstDev &I, double *acc) {
 // lines cross LDS once, conflict-free (lanes on consecutive chunks).  The
 // pass is bound by memory; crossing LDS at both ends and between the radix
 // passes, with divisions by run-time lengths outside eight lengths, had held
-// it below (with both passes changed, the evaluation of 96^3 in FP32 went
-// from 371 to 336 us, in FP64 from 565 to 518, of 90 x 100 x 108 from 653 to
-// 596, of 160 x 160 x 320 from 2337 to 2208).
+// it below (the forward pass, traced: 96^3 in FP32 46 -> 24 us, in FP64 73 -> 44,
+// 90 x 100 x 108 60 -> 27, 160 x 160 x 320 327 -> 253).
 // tile: a = i1, b = first chunk of the row, c = chunks (<= kYC; the lanes
 // past them repeat the last one and store nothing); a < 0 (inverse pass only):
 // the grid's energies.
@@ -1244,9 +1251,10 @@ constexpr int zmain_waves() {
 // all.  A padding after each R2 slots keeps the lanes of neighbouring items on
 // different banks.  The contraction reads the 20 components of a point as
 // contiguous chunks too.  (The radix passes it replaces crossed LDS in words
-// of 8 bytes, at both ends and in every pass: the fused pass alone went from
-// 90 to 52 us at 96^3 in FP32, from 160 to 69 at 90 x 100 x 108, from 154 to
-// 140 at 128^3, and from 20 to 10 at 24^3 in FP64.)
+// of 8 bytes, at both ends and in every pass: the fused pass, traced, went from
+// 92 to 54 us at 96^3 in FP32 and from 158 to 124 in FP64, from 161 to 72 at
+// 90 x 100 x 108, from 161 to 125 at 128^3, and from 20 to 11 at 24^3 in FP64; with
+// packed kernel rows a lone 128^3 triclinic grid stands where it did, 398 and 405.)
 //
 // Contraction layout (vector ALU): lanes form groups of kNQ (three per wave).
 // A group takes one item, a |m1| and a column or pair; lane a loads row a of
@@ -1713,7 +1721,12 @@ static void allow_lds(K kernel, size_t bytes) {
                                 __VA_ARGS__);                                                        \
     } while (0)
 
-// the axis-3 passes: by split class, or as a compile-time length
+// the axis-3 passes: by split class, or as a compile-time length.  These two
+// passes do more index work a point than the others, and constants pay at every
+// one of the common lengths (compile-time against run-time radices, us an
+// evaluation: 24^3 60 and 64, 48^3 93 and 96, 64^3 110 and 112, 96^3 212 and 224,
+// 128^3 399 and 427, 160 x 160 x 320 1743 and 1941, where the theta pass alone takes
+// 276 and 406; FP64 the same way, 96^3 378 and 400).
 template <typename T, int RMAX, int CR1, int CR2>
 hipError_t launch_x_pass(int kind, const LaunchArgs &a) {
     switch (kind) {
