@@ -279,8 +279,9 @@ int vdwnl_log_qmesh(int32_t nq, double q1, double q_c, double lambda, double *q_
  * writes the kinds the planned mode launches, in launch order, into kinds[]
  * (at most max_passes) and returns their number.  Passes that run in another's
  * launch show there: the gradient's directions (all in x_deriv in
- * orthorhombic cells) and the energy reduction (in y_20i).  Timed evaluations
- * launch their passes one by one (no graph). */
+ * orthorhombic cells, axes 3 and 2 in general ones) and the energy reduction
+ * (in y_20i); their own entries are then the gap between two events.  Timed
+ * evaluations launch their passes one by one (no graph). */
 int vdwnl_set_timing(vdwnl_ctx *ctx, int32_t on);
 int vdwnl_pass_times(const vdwnl_ctx *ctx, int32_t max_passes, double *ms, int64_t *calls);
 const char *vdwnl_pass_name(int32_t i);

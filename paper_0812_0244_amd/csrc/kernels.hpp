@@ -274,11 +274,12 @@ __device__ __forceinline__ void load_consts(const Consts *cst, T *qm, T *Mm, T *
 // items on different banks.
 // Compile-time radices (CR1 CR2 = the length; 0: run-time ones) turn the
 // positions and strides of the common lengths into constants.
-// Both passes are bound by the arithmetic and latency of the local chain between
-// their loads and stores.  Against whole lines in radix passes (theta, assembly,
+// Both passes are bound by vector ALU issue (0.85 and 0.92 of the cycles at
+// 128^3 in FP32): the local chain, some 800 instructions a point.  Against whole lines in radix passes (theta, assembly,
 // traced): 90 x 100 x 108 in FP32 87 -> 43 us and 90 -> 36, 96^3 39 -> 31 and
-// 37 -> 32, 160 x 160 x 320 331 -> 268 and 328 -> 331; at 128^3, whose lines had
-// three passes of radix 8 and 4, 61 -> 60 and 55 -> 66.
+// 37 -> 31, 160 x 160 x 320 337 -> 265 and 330 -> 328; lost at two lengths that had
+// compile-time plans: 128^3 60 -> 60 and 55 -> 66, sixteen 64^3 109 -> 130 and
+// 117 -> 139.
 template <typename T, int CR1, int CR2>
 struct XTile {
     static constexpr int kP = kNQ / 2;                        // pair lines per row
@@ -1252,9 +1253,9 @@ constexpr int zmain_waves() {
 // different banks.  The contraction reads the 20 components of a point as
 // contiguous chunks too.  (The radix passes it replaces crossed LDS in words
 // of 8 bytes, at both ends and in every pass: the fused pass, traced, went from
-// 92 to 54 us at 96^3 in FP32 and from 158 to 124 in FP64, from 161 to 72 at
-// 90 x 100 x 108, from 161 to 125 at 128^3, and from 20 to 11 at 24^3 in FP64; with
-// packed kernel rows a lone 128^3 triclinic grid stands where it did, 398 and 405.)
+// 92 to 55 us at 96^3 in FP32 and from 158 to 127 in FP64, from 162 to 70 at
+// 90 x 100 x 108, from 160 to 122 at 128^3, and from 20 to 10 at 24^3 in FP64; with
+// packed kernel rows a lone 128^3 triclinic grid stands where it did, at 405.)
 //
 // Contraction layout (vector ALU): lanes form groups of kNQ (three per wave).
 // A group takes one item, a |m1| and a column or pair; lane a loads row a of
